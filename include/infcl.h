@@ -72,7 +72,10 @@ typedef enum { INFCL_BF16 = 0, INFCL_F32 = 1, INFCL_F16 = 2 } infcl_dtype;
  * The same workspace size serves both calls.  It is linear in b: a few
  * vectors of b floats, plus, when d is not a multiple of 128 (16-bit) or 64
  * (f32), the padded copies of img and txt and the padded gradients
- * (2 b d' fp32 elements, d' the padded width).  Returns INFCL_ERR_INVALID for
+ * (2 b d' fp32 elements, d' the padded width), plus at most 64 MiB of
+ * partial gradient sums where row blocks are swept in several parts (small
+ * batches, and the remainder of a batch beyond whole rounds of the compute
+ * units).  Returns INFCL_ERR_INVALID for
  * a NULL `bytes` or b < 1, d < 1 or an unknown dtype. */
 infcl_status infcl_workspace_size(int64_t b, int64_t d, int dtype, size_t* bytes);
 

@@ -6,6 +6,7 @@
 
 #include <mutex>
 
+#include "bwd.hpp"
 #include "infcl.h"
 
 namespace infcl {
@@ -25,7 +26,8 @@ bool fwd2_supported(int64_t d, int dtype);
 int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
                const float* scale, const float* lse_r, const float* lse_c, const float* aux, const float* dloss,
                void* dimg, void* dtxt, int gdt, float* dscale, double* dscale64, float* lse2, double* ds_part,
-               float* g16, hipStream_t stream);
+               float* g16, float* part, size_t part_cap, hipStream_t stream);
+BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap);
 bool bwd_supported(int64_t d, int dtype);
 }  // namespace infcl
 
@@ -49,18 +51,30 @@ size_t elem_size(int dtype) { return dtype == INFCL_F32 ? 4 : 2; }
 
 struct Layout {
   int64_t dk;  // the width the sweeps run at
-  size_t rowR, rowL, colR, colL, udiag, ref2, fwd_part, lse2, bwd_part, g16, pad, gpad, total;
+  size_t lse2, bwd_part, g16, pad, gpad, rowR, rowL, colR, colL, udiag, ref2, fwd_part;
+  size_t fwd_total;  // bytes without the backward's partial sums
+  size_t total;
+  size_t part() const { return rowR; }  // the backward's partial sums take the place of the forward's pairs
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Most bytes of partial gradient sums a backward may use beyond the forward's
+// partial pairs, whose place they take: 256 workgroups x 128 rows x 512
+// features x 4 bytes (or 64 rows x 1024), one part for every compute unit.
+constexpr size_t kPartBytes = ((size_t)64 << 20) + 4096;
+
 // Workspace regions, sized for the sweeps that (b, d, dtype) launches: the
-// partial pairs of the forward grid (resident rows: Pc row and Pr column
-// partials per sample; streamed tiles: 4 Pc and Pr), the diagonal, the base-2
-// diagonal references (resident rows only), the loss and dscale partials, the
-// base-2 log-sum-exp vectors of the backward and fp16's G' scale.  A shard of
-// nrows <= b rows needs no more: its grid has at most as many row groups and
-// its row partials are nrows long.
+// base-2 log-sum-exp vectors of the backward, the dscale partials and fp16's
+// G' scale, the padded copies; then the partial pairs of the forward grid
+// (resident rows: Pc row and Pr column partials per sample; streamed tiles:
+// 4 Pc and Pr), the diagonal, the base-2 diagonal references (resident rows
+// only) and the loss partials.  The backward, which no longer needs what the
+// forward left there, keeps the partial sums of split row blocks in the same
+// place, which is enlarged where a whole batch's split needs more.  A shard
+// of nrows <= b rows needs no more of the forward's regions (its grid has at
+// most as many row groups and its row partials are nrows long) and splits its
+// blocks as far as the place allows.
 Layout make_layout(int64_t b, int64_t d, int dtype) {
   Layout L;
   L.dk = kernel_width(d, dtype);
@@ -77,6 +91,11 @@ Layout make_layout(int64_t b, int64_t d, int dtype) {
   ncol = (size_t)Pr;
   size_t off = 0;
   const size_t fb = (size_t)b * sizeof(float);
+  L.lse2 = off; off = align256(off + 2 * fb);
+  L.bwd_part = off; off = align256(off + (size_t)2 * ((b + 63) / 64) * sizeof(double));  // 64 or 128 rows per WG
+  L.g16 = off; off = align256(off + (dtype == INFCL_F16 ? (size_t)(2 + 2 * ((b + 255) / 256)) * sizeof(float) : 0));
+  L.pad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * elem_size(dtype) : 0));  // img, txt
+  L.gpad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * sizeof(float) : 0));  // dimg, dtxt
   L.rowR = off; off = align256(off + nrow * fb);
   L.rowL = off; off = align256(off + nrow * fb);
   L.colR = off; off = align256(off + ncol * fb);
@@ -84,13 +103,18 @@ Layout make_layout(int64_t b, int64_t d, int dtype) {
   L.udiag = off; off = align256(off + fb);
   L.ref2 = off; off = align256(off + (resident ? fb : 0));
   L.fwd_part = off; off = align256(off + (size_t)((b + 255) / 256) * sizeof(double));
-  L.lse2 = off; off = align256(off + 2 * fb);
-  L.bwd_part = off; off = align256(off + (size_t)2 * ((b + 63) / 64) * sizeof(double));  // 64 or 128 rows per WG
-  L.g16 = off; off = align256(off + (dtype == INFCL_F16 ? (size_t)(2 + 2 * ((b + 255) / 256)) * sizeof(float) : 0));
-  L.pad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * elem_size(dtype) : 0));  // img, txt
-  L.gpad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * sizeof(float) : 0));  // dimg, dtxt
-  L.total = off;
+  L.fwd_total = off;
+  const size_t part = align256(infcl::plan_bwd(b, b, L.dk, dtype, kPartBytes).part_bytes);
+  L.total = L.part() + part > off ? L.part() + part : off;
   return L;
+}
+
+// Bytes of partial sums a backward call may use: what the layout holds there,
+// at most kPartBytes (so that the split, and the bits of the result, follow
+// from the shape alone).
+size_t part_cap(const Layout& L) {
+  const size_t room = L.total - L.part();
+  return room < kPartBytes ? room : kPartBytes;
 }
 
 // Row copy between widths: rows of cin 16-byte chunks into rows of cout
@@ -235,7 +259,7 @@ infcl_status infcl_fwd_noalloc(const void* img, const void* txt, int64_t b, int6
   if (loss64 != nullptr && ((uintptr_t)loss64 % 8) != 0) return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype)) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (L.total > kScratchBytes) return INFCL_ERR_WORKSPACE;
+  if (L.fwd_total > kScratchBytes) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)scratch_address();
   if (ws == nullptr) return INFCL_ERR_HIP;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
@@ -266,7 +290,7 @@ infcl_status infcl_bwd(const void* img, const void* txt, int64_t b, int64_t d, i
   grad_targets(gi, gt, b, d, ges, ws, L);
   int rc = infcl::launch_bwd(img, txt, b, L.dk, dtype, 0, b, scale, lse_r, lse_c, aux, dloss, gi, gt, gk, dscale,
                              nullptr, (float*)(ws + L.lse2), (double*)(ws + L.bwd_part), (float*)(ws + L.g16),
-                             (hipStream_t)stream);
+                             (float*)(ws + L.part()), part_cap(L), (hipStream_t)stream);
   if (rc == 2) return INFCL_ERR_UNSUPPORTED;
   if (rc == 0 && !unstage_grads(dimg, dtxt, b, b, d, ges, ws, L, (hipStream_t)stream)) rc = 1;
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
@@ -331,7 +355,7 @@ infcl_status infcl_bwd_shard(const void* img, const void* txt, int64_t b, int64_
   grad_targets(gi, gt, b, d, ges, ws, L);
   int rc = infcl::launch_bwd(img, txt, b, L.dk, dtype, r0, bs, scale, lse_r, lse_c, aux, dloss, gi, gt, gk, nullptr,
                              dscale_part, (float*)(ws + L.lse2), (double*)(ws + L.bwd_part), (float*)(ws + L.g16),
-                             (hipStream_t)stream);
+                             (float*)(ws + L.part()), part_cap(L), (hipStream_t)stream);
   if (rc == 2) return INFCL_ERR_UNSUPPORTED;
   if (rc == 0 && !unstage_grads(dimg, dtxt, bs, b, d, ges, ws, L, (hipStream_t)stream)) rc = 1;
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;

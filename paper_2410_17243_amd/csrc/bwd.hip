@@ -11,10 +11,10 @@
 //   ds = dloss/(2b) * sum_{i != j} [P^r_ij (u_ij - u_ii) + P^c_ij (u_ij - u_jj)],  u = <img_i, txt_j>.
 //
 // Design (differs from the paper's single pass that read-modify-writes the text
-// gradient tile in HBM for every tile): one kernel template, launched twice.
-// The launch that "owns" the image rows keeps dimg rows in registers and sweeps
-// all text rows; the second launch swaps the roles.  The similarity tile is
-// recomputed in each launch, but no gradient leaves the registers before the
+// gradient tile in HBM for every tile): one kernel, two kinds of row block.
+// A block that "owns" image rows keeps their dimg rows in registers and sweeps
+// all text rows; a block of text rows swaps the roles.  The similarity tile is
+// recomputed for each side, but no gradient leaves the registers before the
 // sweep ends and no atomics are used.  A workgroup owns 128 rows (32 per wave)
 // and sweeps 32-row tiles of the other side.  Per tile and wave:
 //   GEMM1  S^T(32 swept x 32 own) = swept_tile * own^T   (own operand held in
@@ -90,13 +90,18 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform (SGPR)
   const int l32 = lane & 31, h = lane >> 5;
   const int64_t b = p.b;
-  const int64_t wg0 = p.own_off + (int64_t)blockIdx.x * kBwdBM;  // own_off is a multiple of 32
+  const BwdTask task = bwd_task(p, kBwdBM * D);
+  const BwdSide& sd = p.side[task.sd];
+  const char* const swept = (const char*)sd.swept + (int64_t)task.row0 * ROWG;
+  const float* const lse2_swept = sd.lse2_swept + task.row0;
+  const int rows = task.rows, ntile = (rows + kBwdBN - 1) / kBwdBN;
+  const int64_t wg0 = p.own_off + (int64_t)task.rb * kBwdBM;  // own_off is a multiple of 32
   const int64_t own0 = wg0 + 32 * wave;                            // this wave's first own row
   const int64_t iown = own0 + l32;                                 // this lane's own row
   const bool own_ok = iown < p.own_end;
   const int64_t irow = own_ok ? iown : p.own_end - 1;
   const bool wave_rows_ok = own0 + 32 <= p.own_end;
-  const int ntile = (int)((b + kBwdBN - 1) / kBwdBN);
+  const int own0_t = (int)(own0 - task.row0);  // counted from the first swept row
 
   const float s = p.scale[0];
   const float k2 = s * kLog2e;
@@ -110,15 +115,15 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   constexpr int FR = ES == 2 ? 1 : 2;  // 16-byte loads per step and lane
   frag_t ownf[KS][FR];
   {
-    const char* src = (const char*)p.own + (irow * D) * ES;
+    const char* src = (const char*)sd.own + (irow * D) * ES;
 #pragma unroll
     for (int s2 = 0; s2 < KS; ++s2)
 #pragma unroll
       for (int u = 0; u < FR; ++u) ownf[s2][u] = *(const frag_t*)(src + (16 * s2 + 8 * h) * ES + 16 * u);
   }
-  const float aO = own_ok ? p.lse_own[iown] * kLog2e : 0.f;
+  const float aO = own_ok ? sd.lse_own[iown] * kLog2e : 0.f;
   const float uO = own_ok ? p.udiag[iown] : 0.f;
-  const float gdiag = own_ok ? expm1f(-p.ell_own[iown]) + expm1f(-p.ell_swept[iown]) : 0.f;
+  const float gdiag = own_ok ? expm1f(-sd.ell_own[iown]) + expm1f(-sd.ell_swept[iown]) : 0.f;
 
   auto opaque_lane = [&]() {
     int lo = lane;
@@ -134,17 +139,17 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   // offset is one constant and the rest is wave-uniform.  The DMA lane offsets
   // are rebuilt from an opaque lane id at each use: all 512 registers are in
   // use at d = 512, a value held across the loop would be spilled, and a
-  // scratch reload waits for all DMA in flight.  Rows past b fall outside the
-  // resource and load as zeros (their G' is masked); jt < 0 loads zeros only.
-  auto dma_lane_off = [&]() { return sweep_dma_lane_off(opaque_lane(), wave, ROWG); };
-  auto dma_kk_off = [&](int kk) { return sweep_dma_kk_off(kk, wave, ROWG); };
+  // scratch reload waits for all DMA in flight.  Rows past the
+  // end of the sweep fall outside the resource and load as zeros (their G' is masked).
+  // (The wave-uniform rest is the wave's 4 rows, added to the lane part, plus a
+  // compile-time constant, the scalar operand.)
+  auto dma_lane_off = [&]() { return sweep_dma_lane_off(opaque_lane(), wave, ROWG) + 4 * wave * ROWG; };
+  auto dma_kk_off = [&](int kk) { return sweep_dma_kk_off(kk, 0, ROWG); };
   auto tile_rsrc = [&](int jt) {
-    const int64_t j0 = (int64_t)(jt < 0 ? 0 : jt) * kBwdBN;
-    return rsrc_words((const char*)p.swept + j0 * ROWG, jt < 0 ? 0 : (b - j0) * ROWG);
+    return sweep_tile_rsrc(swept + (int64_t)jt * TILEB, rows - jt * kBwdBN, ROWG);
   };
   auto lse_rsrc = [&](int jt) {
-    const int64_t j0 = (int64_t)(jt < 0 ? 0 : jt) * kBwdBN;
-    return rsrc_words(p.lse2_swept + j0, jt < 0 ? 0 : (b - j0) * 4);
+    return sweep_tile_rsrc(lse2_swept + (int64_t)jt * kBwdBN, rows - jt * kBwdBN, 4);
   };
   // The log-sum-exp slot of a tile is loaded by every wave with the full wave
   // (no divergent branch in the middle of GEMM1): lanes 8k..8k+7 all fetch the
@@ -155,7 +160,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
     const u32x4 rs = tile_rsrc(jt);
     const uint32_t lo = dma_lane_off();
 #pragma unroll
-    for (int kk = 0; kk < NIW; ++kk) dma16_asm(rs, dst + 1024 * (wave + 4 * kk), lo + dma_kk_off(kk));
+    for (int kk = 0; kk < NIW; ++kk) dma16_asm(rs, dst + 1024 * (wave + 4 * kk), lo, dma_kk_off(kk));
     dma16_asm(lse_rsrc(jt), ldst, lse_lane_off());
   };
 
@@ -189,7 +194,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
     } else {
       make_offA(opaque_lane(), offA);
     }
-    u32x4 drs = tile_rsrc(-1), drl = lse_rsrc(-1);
+    u32x4 drs = tile_rsrc(0), drl = lse_rsrc(0);
     uint32_t dlo = 0;
     if (with_dma) {
       drs = tile_rsrc(dtile);
@@ -201,7 +206,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       constexpr int SPI = KS / NIW;  // steps per DMA instruction
       if ((s2 + 1) % SPI == 0) {
         const int kk = (s2 + 1) / SPI - 1;
-        dma16_asm(drs, ddst + 1024 * (wave + 4 * kk), dlo + dma_kk_off(kk));
+        dma16_asm(drs, ddst + 1024 * (wave + 4 * kk), dlo, dma_kk_off(kk));
       }
       if (s2 == (KS > 1 ? 1 : 0)) dma16_asm(drl, dlse, lse_lane_off());
     };
@@ -244,43 +249,39 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
 
   // ---- G' of swept tile jt from its S^T block (log2 domain); entry r <->
   // swept row j = 16 (r>>3) + 8h + (r&7) of the tile.  Returns the dscale
-  // contribution.  Tiles touching the diagonal or the ragged end take the
-  // masked path (uniform branch).
+  // contribution.  Tiles touching the diagonal or the end of the sweep take
+  // the masked path (uniform branch).  Own rows past the end need no mask:
+  // each own row feeds its own gradient row only, which is not stored, and
+  // its dscale sum is dropped after the sweep.
   auto tile_special = [&](int jt) {
-    const int64_t j0 = (int64_t)jt * kBwdBN;
-    return (j0 == own0) || (j0 + kBwdBN > b) || !wave_rows_ok;
+    const int j0 = jt * kBwdBN;
+    return (j0 == own0_t) || (j0 + kBwdBN > rows);
   };
   auto epilogue = [&](int jt, const INFCL_LDS float* lsep, const f32x16& sacc, float (&gv)[16]) -> float {
-    const int64_t j0 = (int64_t)jt * kBwdBN;
+    const int j0 = jt * kBwdBN;
+    const bool special = tile_special(jt);
+    const int lo = opaque_lane();  // (the masks' lane parts are rebuilt per use: held, they would spill)
+    const int jl = j0 + 8 * (lo >> 5), iown_t = own0_t + (lo & 31);
     float ds_tile = 0.f;
-    if (!tile_special(jt)) {
-      const INFCL_LDS char* lp = (const INFCL_LDS char*)lsep + 32 * h;
+    const INFCL_LDS char* lp = (const INFCL_LDS char*)lsep + 32 * h;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 v = *(const INFCL_LDS f32x4*)(lp + 64 * (q4 >> 1) + 16 * (q4 & 1));
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const f32x4 v = *(const INFCL_LDS f32x4*)(lp + 64 * (q4 >> 1) + 16 * (q4 & 1));
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int r = 4 * q4 + c;
-          const float pO = exp2_hw(__builtin_fmaf(sacc[r], k2, -aO));
-          const float pS = exp2_hw(__builtin_fmaf(sacc[r], k2, -v[c]));
-          gv[r] = pO + pS;
-          ds_tile = __builtin_fmaf(pO, sacc[r] - uO, ds_tile);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t j = j0 + 16 * (r >> 3) + 8 * h + (r & 7);
-        const bool jok = j < b;
-        const float aSr = p.lse2_swept[jok ? j : b - 1];
+      for (int c = 0; c < 4; ++c) {
+        const int r = 4 * q4 + c;
         const float pO = exp2_hw(__builtin_fmaf(sacc[r], k2, -aO));
-        const float pS = exp2_hw(__builtin_fmaf(sacc[r], k2, -aSr));
-        const bool ok = own_ok && jok;
-        const bool dg = (j == iown);
-        float gg = ok ? pO + pS : 0.f;
-        gg = dg ? gdiag : gg;
-        gv[r] = gg;
-        ds_tile += (ok && !dg) ? pO * (sacc[r] - uO) : 0.f;
+        const float pS = exp2_hw(__builtin_fmaf(sacc[r], k2, -v[c]));
+        gv[r] = pO + pS;
+        if (!special) {
+          ds_tile = __builtin_fmaf(pO, sacc[r] - uO, ds_tile);
+        } else {
+          const int j = jl + 16 * (r >> 3) + (r & 7);
+          const bool jok = j < rows;
+          const bool dg = j == iown_t;
+          gv[r] = jok ? (dg ? gdiag : gv[r]) : 0.f;
+          ds_tile += (bool)(jok & !dg) ? pO * (sacc[r] - uO) : 0.f;
+        }
       }
     }
     return ds_tile;
@@ -421,13 +422,13 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       // (issuing the loads of tile jt+2), then GEMM2 of tile jt together with
       // the G' of tile jt+1.  Three tile buffers rotate; G' buffers alternate.
       // Past the last tile, GEMM1 runs on a stale buffer and the G' step takes
-      // the masked path (tile rows >= b), so it yields zeros.
+      // the masked path (rows past the sweep's end), so it yields zeros.
       issue_tile(0, tA, lA);
-      issue_tile(ntile > 1 ? 1 : -1, tB, lB);
+      issue_tile(1, tB, lB);
       wait_dma();
       __syncthreads();
       {
-        const f32x16 sacc = gemm1(tA, false, -1, tC, lC);
+        const f32x16 sacc = gemm1(tA, false, 0, tC, lC);
         float gv[16];
         const float d0 = epilogue(0, lA, sacc, gv);
         if (pass == 0) ds_acc += (double)d0;
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       auto body = [&](int jt, const INFCL_LDS char* cur, INFCL_LDS char* nxt, const INFCL_LDS float* lnxt,
                       INFCL_LDS char* fre, INFCL_LDS float* lfre) {
         const bool next = jt + 1 < ntile;
-        const f32x16 sacc = gemm1(nxt, true, jt + 2 < ntile ? jt + 2 : -1, fre, lfre);
+        const f32x16 sacc = gemm1(nxt, true, jt + 2, fre, lfre);
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 ga[2];
         float dn = gemm2_staged(true, cur, gp + (jt & 1) * kGpBytes, lnxt, sacc, ga);
@@ -458,7 +459,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         __syncthreads();
       };
       // Unrolled over the buffer rotation without tests in between: a tile
-      // index past the end is a tile of rows past b, fully masked (zero G').
+      // index past the end is a tile of rows past the end, fully masked (zero G').
       for (int jt = 0; jt < ntile; jt += 3) {
         body(jt, tA, tB, lB, tC, lC);
         body(jt + 1, tB, tC, lC, tA, lA);
@@ -472,7 +473,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       __syncthreads();
       auto body = [&](int jt, const INFCL_LDS char* cur, const INFCL_LDS float* lcur, INFCL_LDS char* nxt,
                       INFCL_LDS float* lnxt) {
-        const f32x16 sacc = gemm1(cur, true, jt + 1 < ntile ? jt + 1 : -1, nxt, lnxt);
+        const f32x16 sacc = gemm1(cur, true, jt + 1, nxt, lnxt);
         float gv[16];
         const float d0 = epilogue(jt, lcur, sacc, gv);
         if (pass == 0) ds_acc += (double)d0;
@@ -489,49 +490,107 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         __syncthreads();
       };
       // Unrolled over the buffer pair without a test in between: a tile
-      // index past the end is a tile of rows past b, fully masked (zero G').
+      // index past the end is a tile of rows past the end, fully masked (zero G').
       for (int jt = 0; jt < ntile; jt += 2) {
         body(jt, tA, lA, tB, lB);
         body(jt + 1, tB, lB, tA, lA);
       }
     }
 
-    // ---- write dOwn: lane holds feature l32 of a 32-feature block, rows 8(r>>2)+4h+(r&3)
+    // ---- write dOwn (or this part's unscaled sums): lane holds feature l32 of
+    // a 32-feature block, rows 8(r>>2)+4h+(r&3)
     if constexpr (ES == 2) {
-      const bool all_ok = wg0 + kBwdBM <= p.own_end;
+      const int rl0 = 4 * h, f0 = 32 * (pass * FB + wave * FBW) + l32;
+      if (task.part) {
 #pragma unroll
-      for (int ob = 0; ob < 4; ++ob) {
-        auto* dst = (typename GO::type*)p.dOwn + (wg0 - p.own_off + 32 * ob + 4 * h) * D + 32 * (pass * FB + wave * FBW) + l32;
+        for (int ob = 0; ob < 4; ++ob) {
+          float* dst = task.part + (32 * ob + rl0) * D + f0;
 #pragma unroll
-        for (int fbw = 0; fbw < FBW; ++fbw)
+          for (int fbw = 0; fbw < FBW; ++fbw)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int64_t row = wg0 + 32 * ob + 8 * (r >> 2) + 4 * h + (r & 3);
-            if (all_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[ob * FBW + fbw][r]);
-          }
+            for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = dacc[ob * FBW + fbw][r];
+        }
+      } else {
+        const bool all_ok = wg0 + kBwdBM <= p.own_end;
+#pragma unroll
+        for (int ob = 0; ob < 4; ++ob) {
+          auto* dst = (typename GO::type*)sd.dOwn + (wg0 - p.own_off + 32 * ob + rl0) * D + f0;
+#pragma unroll
+          for (int fbw = 0; fbw < FBW; ++fbw)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int64_t row = wg0 + 32 * ob + 8 * (r >> 2) + rl0 + (r & 3);
+              if (all_ok || row < p.own_end)
+                dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[ob * FBW + fbw][r]);
+            }
+        }
       }
     } else {
-      auto* dst = (typename GO::type*)p.dOwn + (own0 - p.own_off + 4 * h) * D + 32 * pass * FB + l32;
+      const int f0 = 32 * pass * FB + l32;
+      if (task.part) {
+        float* dst = task.part + (32 * wave + 4 * h) * D + f0;
 #pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
+        for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t row = own0 + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (wave_rows_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fb] = GO::cvt(kfin * dacc[fb][r]);
-        }
+          for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fb] = dacc[fb][r];
+      } else {
+        auto* dst = (typename GO::type*)sd.dOwn + (own0 - p.own_off + 4 * h) * D + f0;
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int64_t row = own0 + 8 * (r >> 2) + 4 * h + (r & 3);
+            if (wave_rows_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fb] = GO::cvt(kfin * dacc[fb][r]);
+          }
+      }
     }
     // the next pass reuses the tile buffers
     __syncthreads();
   }
 
   // ---- dscale partial of this workgroup: fixed-order reduction
-  red[threadIdx.x] = ds_acc;
+  red[threadIdx.x] = own_ok ? ds_acc : 0.0;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
   if (threadIdx.x == 0) p.ds_part[blockIdx.x] = red[0];
+}
+
+// Gradients of the split row blocks: the ns partial sums of each element in
+// fixed order, scaled as the sweeps scale theirs and rounded once to the
+// gradient type.  Bound by memory (the partials are read once, 16 bytes per
+// lane); at most kPartBytes of them, which stay in the last-level cache.
+template <bool G16, bool F16>
+__global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm) {
+  using GO = GradOut<G16, F16>;
+  const int c4 = (int)(p.d >> 2);  // 4-feature groups per row
+  const int per = bm * c4;         // ... per block
+  const int q = blockIdx.y;
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int blk = p.nfull + q;
+  const int sd = blk >= p.nblk ? 1 : 0;
+  const int rl = e / c4;
+  const int64_t row = (int64_t)(sd ? blk - p.nblk : blk) * bm + rl;  // own row - own_off
+  if (e >= per || row >= p.own_end - p.own_off) return;
+  const float s = p.scale[0];
+  const float dl = p.dloss ? p.dloss[0] : 1.0f;
+  const float kfin = dl * s / (2.0f * (float)p.b) * (F16 ? p.g16[1] : 1.0f);
+  const f32x4* src = (const f32x4*)(p.part + (int64_t)q * p.ns * per * 4) + e;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  int k = 0;
+  for (; k + 4 <= p.ns; k += 4) {  // four loads in flight, added in order
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = src[(int64_t)(k + u) * per];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a += v[u];
+  }
+  for (; k < p.ns; ++k) a += src[(int64_t)k * per];
+  auto* dst = (typename GO::type*)p.side[sd].dOwn + row * p.d + 4 * (e - rl * c4);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) dst[u] = GO::cvt(kfin * a[u]);
 }
 
 // dscale = dloss / (2b) * (sum of both launches' partials), fixed order; into
@@ -692,8 +751,55 @@ __global__ void __launch_bounds__(256) lse_to_log2(const float* lse_r, const flo
 }
 
 bool bwd_wide_supported(int64_t d, int dtype);
-int bwd_wide_workgroups(int64_t nown);
 int launch_bwd_wide(const BwdParams& p, int nwg, bool f16, hipStream_t stream);
+
+// Split of the backward over workgroups, for nrows own rows of each side
+// against b swept rows: both sides' row blocks run in one launch, and the
+// blocks beyond the last whole round of kCUs are swept in ns parts each, so
+// that a batch of few blocks, or the remainder of a larger one, still fills
+// the chip (measured, one launch per side before, step with the forward:
+// b = 1024, d = 512 fp32 1834 -> 179 us, b = 4096, d = 768 fp16 456 -> 202 us,
+// b = 8192, d = 256 fp32 4.60 -> 1.44 ms).  ns minimises (rounds of parts) / ns block times plus the cost of
+// a part (prologue, epilogue) and of the reduction, which reads and writes
+// bm x d floats per part; the partial sums take at most cap bytes.
+constexpr int kCUs = 256;
+BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
+  BwdPlan pl;
+  pl.bm = bwd_wide_supported(d, dtype) ? kWideBM : kBwdBM;
+  pl.nblk = (int)((nrows + pl.bm - 1) / pl.bm);
+  const int total = 2 * pl.nblk;
+  const int64_t ntile = (b + kBwdBN - 1) / kBwdBN;
+  pl.nfull = total / kCUs * kCUs;
+  pl.ns = 1;
+  pl.part_bytes = 0;
+  const int rem = total - pl.nfull;
+  if (rem > 0) {
+    // microseconds: a tile, a part's fixed cost, a part's bytes through the reduction
+    const double t_tile = dtype == 1 ? 2.0e-5 * (double)(d * d) + 0.02 * (double)d : 3.7e-3 * (double)d;
+    const double blk_bytes = (double)pl.bm * (double)d * 4.0;
+    double best = 0.0;
+    for (int ns = 1; ns <= 64 && ns <= ntile; ++ns) {
+      const int64_t parts = (int64_t)rem * ns;
+      const double bytes = (double)parts * blk_bytes;
+      if (ns > 1 && bytes + 8.0 * (double)(pl.nfull + parts) > (double)cap) break;
+      const double rounds = (double)((parts + kCUs - 1) / kCUs);
+      double t = rounds * (8.0 + t_tile * (double)((ntile + ns - 1) / ns));
+      if (ns > 1) t += 6.0 + bytes / 2.0e6;
+      if (ns == 1 || t < best) {
+        best = t;
+        pl.ns = ns;
+      }
+    }
+  }
+  pl.nwg = pl.nfull + rem * pl.ns;
+  if (pl.ns > 1) {
+    const size_t sums = (size_t)rem * pl.ns * (size_t)pl.bm * (size_t)d * sizeof(float);
+    pl.part_bytes = sums + (size_t)pl.nwg * sizeof(double);  // the sums, then the dscale partials
+  } else {
+    pl.nfull = total;
+  }
+  return pl;
+}
 
 // Backward: 16-bit inputs with d = 768 or 1024 take the single-pass wide-row sweep
 // (64 own rows per workgroup), everything else the 128-row sweep above.  Own
@@ -701,19 +807,13 @@ int launch_bwd_wide(const BwdParams& p, int nwg, bool f16, hipStream_t stream);
 // shard's samples otherwise, with dimg/dtxt [nrows, d]: fp32, or with gdt = 1
 // the 16-bit input type); lse_r, lse_c and aux cover all b samples.  dscale
 // (fp32) and/or dscale64 (fp64) receive this call's share, dloss/(2b) times its
-// partial sums.
+// partial sums.  part: the partial sums of split row blocks, part_cap bytes.
 int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
                const float* scale, const float* lse_r, const float* lse_c, const float* aux, const float* dloss,
                void* dimg, void* dtxt, int gdt, float* dscale, double* dscale64, float* lse2, double* ds_part,
-               float* g16, hipStream_t stream) {
+               float* g16, float* part, size_t part_cap, hipStream_t stream) {
   const bool wide = bwd_wide_supported(d, dtype);
-  const int nwg = wide ? bwd_wide_workgroups(nrows) : (int)((nrows + kBwdBM - 1) / kBwdBM);
-  auto launch = [&](const BwdParams& q) {
-    if (wide) return launch_bwd_wide(q, nwg, dtype == 2, stream);
-    if (dtype == 0) return launch_bwd_t<__bf16>(q, nwg, stream);
-    if (dtype == 2) return launch_bwd_t<_Float16>(q, nwg, stream);
-    return launch_bwd_t<float>(q, nwg, stream);
-  };
+  const BwdPlan pl = plan_bwd(b, nrows, d, dtype, part_cap);
   float* l2r = lse2;
   float* l2c = lse2 + b;
   const unsigned nblk = (unsigned)((b + 255) / 256);
@@ -734,29 +834,37 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
   p.own_off = r0;
   p.own_end = r0 + nrows;
   p.gdt = gdt;
-  // launch 1: own = image rows (dimg), swept = text rows
-  p.own = img;
-  p.swept = txt;
-  p.lse_own = lse_r;
-  p.lse2_swept = l2c;
-  p.ell_own = aux;
-  p.ell_swept = aux + b;
-  p.dOwn = dimg;
-  p.ds_part = ds_part;
-  int rc = launch(p);
+  p.side[0] = BwdSide{img, txt, lse_r, l2c, aux, aux + b, dimg};
+  p.side[1] = BwdSide{txt, img, lse_c, l2r, aux + b, aux, dtxt};
+  p.nblk = pl.nblk;
+  p.nfull = pl.nfull;
+  p.ns = pl.ns;
+  p.part = part;
+  const int64_t split = 2 * (int64_t)pl.nblk - pl.nfull;  // split row blocks
+  p.ds_part = pl.ns > 1 ? (double*)(part + split * pl.ns * pl.bm * d) : ds_part;
+  int rc;
+  if (wide)
+    rc = launch_bwd_wide(p, pl.nwg, dtype == 2, stream);
+  else if (dtype == 0)
+    rc = launch_bwd_t<__bf16>(p, pl.nwg, stream);
+  else if (dtype == 2)
+    rc = launch_bwd_t<_Float16>(p, pl.nwg, stream);
+  else
+    rc = launch_bwd_t<float>(p, pl.nwg, stream);
   if (rc) return rc;
-  // launch 2: own = text rows (dtxt), swept = image rows
-  p.own = txt;
-  p.swept = img;
-  p.lse_own = lse_c;
-  p.lse2_swept = l2r;
-  p.ell_own = aux + b;
-  p.ell_swept = aux;
-  p.dOwn = dtxt;
-  p.ds_part = ds_part + nwg;
-  rc = launch(p);
-  if (rc) return rc;
-  hipLaunchKernelGGL(dscale_finish, dim3(1), dim3(256), 0, stream, (const double*)ds_part, (int64_t)2 * nwg, b,
+  if (pl.ns > 1) {
+    const dim3 grid((unsigned)((pl.bm * (d >> 2) + 255) / 256), (unsigned)split);
+    if (dtype == 2 && gdt)
+      hipLaunchKernelGGL((bwd_reduce<true, true>), grid, dim3(256), 0, stream, p, pl.bm);
+    else if (dtype == 2)
+      hipLaunchKernelGGL((bwd_reduce<false, true>), grid, dim3(256), 0, stream, p, pl.bm);
+    else if (gdt)
+      hipLaunchKernelGGL((bwd_reduce<true, false>), grid, dim3(256), 0, stream, p, pl.bm);
+    else
+      hipLaunchKernelGGL((bwd_reduce<false, false>), grid, dim3(256), 0, stream, p, pl.bm);
+    if (hipGetLastError() != hipSuccess) return 1;
+  }
+  hipLaunchKernelGGL(dscale_finish, dim3(1), dim3(256), 0, stream, (const double*)p.ds_part, (int64_t)pl.nwg, b,
                      dloss, dscale, dscale64);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }

@@ -5,26 +5,82 @@
 
 namespace infcl {
 
-struct BwdParams {
-  const void* own;    // [b, d] rows whose gradient this launch produces
+constexpr int kBwdBN = kSweepBN;  // swept rows per tile
+
+// One side of the backward: own rows get a gradient, the other modality is swept.
+struct BwdSide {
+  const void* own;    // [b, d] rows whose gradient is produced
   const void* swept;  // [b, d] the other modality
-  int64_t b, d;
-  const float* scale;
   const float* lse_own;     // [b]  natural-log log-sum-exp of the own side
   const float* lse2_swept;  // [b]  log-sum-exp of the swept side times log2(e)
   const float* ell_own;     // [b]  r_i - x_ii of the own side
   const float* ell_swept;   // [b]
-  const float* udiag;       // [b]  <img_i, txt_i>
-  const float* dloss;       // device scalar or nullptr (= 1)
-  int64_t own_off, own_end;  // own rows [own_off, own_end) (a shard; 0 and b for the whole batch)
   void* dOwn;               // [own_end - own_off, d], by own row - own_off: fp32, or with gdt = 1 the
                             // input's 16-bit type
-  double* ds_part;          // [gridDim.x]
-  const float* g16;         // fp16 inputs: (alpha, 1/alpha), the power of two G' is scaled by
-  int gdt;                  // gradient type, which chooses the kernel instantiation: 0 fp32, 1 16-bit
 };
 
-constexpr int kBwdBN = kSweepBN;  // swept rows per tile
+struct BwdParams {
+  BwdSide side[2];  // image rows owned, text rows owned
+  int64_t b, d;
+  const float* scale;
+  const float* udiag;  // [b]  <img_i, txt_i>
+  const float* dloss;  // device scalar or nullptr (= 1)
+  int64_t own_off, own_end;  // own rows [own_off, own_end) of both sides (a shard; 0 and b for the whole batch)
+  double* ds_part;           // [gridDim.x]
+  const float* g16;          // fp16 inputs: (alpha, 1/alpha), the power of two G' is scaled by
+  int gdt;                   // gradient type, which chooses the kernel instantiation: 0 fp32, 1 16-bit
+  // Work split (plan_bwd): of the 2 nblk row blocks (image side first) the
+  // first nfull are swept whole, one workgroup each; each of the others is
+  // swept by ns workgroups, a contiguous range of tiles each, whose unscaled
+  // fp32 sums go to part[(block - nfull) ns + k][rows][d] for bwd_reduce.
+  int nblk, nfull, ns;
+  float* part;
+};
+
+// A workgroup's share of the plan: its side, row block and swept rows
+// [row0, row0 + rows), row0 a multiple of the tile, and with ns > 1 the slot
+// of its partial sums (nullptr: final gradients).  The sweeps count tiles and
+// rows from row0.
+struct BwdTask {
+  int sd, rb, row0, rows;
+  float* part;
+};
+__device__ __forceinline__ BwdTask bwd_task(const BwdParams& p, int bm_d) {
+  // (readfirstlane: the compiler divides on the vector unit and would keep the
+  // wave-uniform results in vector registers for the whole sweep)
+  BwdTask t;
+  const int wg = blockIdx.x;
+  int blk = wg;
+  t.row0 = 0;
+  t.rows = (int)p.b;  // at most 2^30
+  t.part = nullptr;
+  if (p.ns > 1 && wg >= p.nfull) {
+    const uint32_t ntile = ((uint32_t)p.b + kBwdBN - 1) / kBwdBN;
+    const uint32_t r = wg - p.nfull, ns = p.ns;
+    const uint32_t q = __builtin_amdgcn_readfirstlane(r / ns), k = r - q * ns;
+    blk = p.nfull + (int)q;
+    // ntile k < 2^31: ntile <= 2^25, k < ns <= 64
+    const int t0 = (int)__builtin_amdgcn_readfirstlane(ntile * k / ns);
+    const int t1 = (int)__builtin_amdgcn_readfirstlane(ntile * (k + 1) / ns);
+    t.row0 = t0 * kBwdBN;
+    t.rows = (t1 == (int)ntile ? (int)p.b : t1 * kBwdBN) - t.row0;
+    t.part = p.part + (int64_t)r * bm_d;
+  }
+  t.sd = blk >= p.nblk ? 1 : 0;
+  t.rb = t.sd ? blk - p.nblk : blk;
+  return t;
+}
+
+// How a backward call is split over workgroups (see plan_bwd in bwd.hip).
+struct BwdPlan {
+  int bm;           // own rows per row block
+  int nblk;         // row blocks per side
+  int nfull, ns;    // blocks swept whole; parts of each other block
+  int nwg;          // workgroups
+  size_t part_bytes;  // partial sums and dscale partials (0 when nothing is split)
+};
+
+constexpr int kWideBM = 64;  // own rows per workgroup of the wide-row sweeps
 
 // Gradient element type of a sweep: fp32, or with G16 the 16-bit input type
 // (fp16 with F16, else bf16), rounded to nearest even from the fp32 gradient

@@ -34,8 +34,6 @@
 
 namespace infcl {
 
-constexpr int kWideBM = 64;  // own rows per workgroup
-
 template <int D, bool F16, bool G16>
 __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   using GO = GradOut<G16, F16>;  // gradient element type
@@ -69,13 +67,17 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   const int ob = wave >> 1, kh = wave & 1;  // own block, feature half of GEMM1
   const int l32 = lane & 31, h = lane >> 5;
   const int64_t b = p.b;
-  const int64_t wg0 = p.own_off + (int64_t)blockIdx.x * kWideBM;  // own_off is a multiple of 32
+  const BwdTask task = bwd_task(p, kWideBM * D);
+  const BwdSide& sd = p.side[task.sd];
+  const char* const swept = (const char*)sd.swept + (int64_t)task.row0 * ROWG;
+  const float* const lse2_swept = sd.lse2_swept + task.row0;
+  const int rows = task.rows, ntile = (rows + kBwdBN - 1) / kBwdBN;
+  const int64_t wg0 = p.own_off + (int64_t)task.rb * kWideBM;  // own_off is a multiple of 32
   const int64_t own0 = wg0 + 32 * ob;                              // this wave's own block
   const int64_t iown = own0 + l32;
   const bool own_ok = iown < p.own_end;
   const int64_t irow = own_ok ? iown : p.own_end - 1;
-  const bool wave_rows_ok = own0 + 32 <= p.own_end;
-  const int ntile = (int)((b + kBwdBN - 1) / kBwdBN);
+  const int own0_t = (int)(own0 - task.row0);  // counted from the first swept row
 
   const float s = p.scale[0];
   const float k2 = s * kLog2e;
@@ -87,13 +89,13 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   // own operand of GEMM1: row irow, features kh d/2 + 16 s2 + 8h .. +8
   bf16x8 ownf[KH];
   {
-    const __bf16* src = (const __bf16*)p.own + irow * D + kh * (D / 2) + 8 * h;
+    const __bf16* src = (const __bf16*)sd.own + irow * D + kh * (D / 2) + 8 * h;
 #pragma unroll
     for (int s2 = 0; s2 < KH; ++s2) ownf[s2] = *(const bf16x8*)(src + 16 * s2);
   }
-  const float aO = own_ok ? p.lse_own[iown] * kLog2e : 0.f;
+  const float aO = own_ok ? sd.lse_own[iown] * kLog2e : 0.f;
   const float uO = own_ok ? p.udiag[iown] : 0.f;
-  const float gdiag = own_ok ? expm1f(-p.ell_own[iown]) + expm1f(-p.ell_swept[iown]) : 0.f;
+  const float gdiag = own_ok ? expm1f(-sd.ell_own[iown]) + expm1f(-sd.ell_swept[iown]) : 0.f;
 
   auto opaque_lane = [&]() {
     int lo = lane;
@@ -101,18 +103,18 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
     return lo;
   };
   auto tile_rsrc = [&](int jt) {
-    const int64_t j0 = (int64_t)(jt < 0 ? 0 : jt) * kBwdBN;
-    return rsrc_words((const char*)p.swept + j0 * ROWG, jt < 0 ? 0 : (b - j0) * ROWG);
+    return sweep_tile_rsrc(swept + (int64_t)jt * TILEB, rows - jt * kBwdBN, ROWG);
   };
   auto lse_rsrc = [&](int jt) {
-    const int64_t j0 = (int64_t)(jt < 0 ? 0 : jt) * kBwdBN;
-    return rsrc_words(p.lse2_swept + j0, jt < 0 ? 0 : (b - j0) * 4);
+    return sweep_tile_rsrc(lse2_swept + (int64_t)jt * kBwdBN, rows - jt * kBwdBN, 4);
   };
   auto lse_lane_off = [&]() { return 16u * (uint32_t)(opaque_lane() & 7); };
   // Per-lane address parts are rebuilt at each use from an opaque lane id:
   // at d = 1024 all 512 registers are taken, so a value held across the loop
   // would be spilled, and a scratch reload waits for all DMA in flight.
-  auto dma_lo = [&]() { return sweep_dma_lane_off(opaque_lane(), wave, ROWG); };
+  // (the instruction's part of the DMA offset is the wave's 4 rows, kept in
+  // the lane part, plus a compile-time constant, the scalar operand)
+  auto dma_lo = [&]() { return sweep_dma_lane_off(opaque_lane(), wave, ROWG) + 4 * wave * ROWG; };
   // The kh = 1 wave loads the tile's rows 16..31 into MFMA rows 0..15 and
   // rows 0..15 into 16..31 (row index XOR 16; the row does not enter the bank
   // of a chunk): accumulator entries 0..7 of either wave are then the ones it
@@ -165,6 +167,14 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
     return sacc;
   };
 
+  // G' entry of the lane's own row against a swept row with base-2 LSE Lj
+  auto gp_entry = [&](float x, float Lj, float& ds) {
+    const float pO = exp2_hw(__builtin_fmaf(x, k2, -aO));
+    const float pS = exp2_hw(__builtin_fmaf(x, k2, -Lj));
+    ds = __builtin_fmaf(pO, x - uO, ds);
+    return F16 ? (pO + pS) * g16a : pO + pS;
+  };
+
   // ---- join, G' of the wave's 8 entries (entry i <-> swept row
   // 16 kh + 8h + i of the tile) into the G' block, with the DMA of tile
   // dtile into ddst spread over the entries; returns dscale's share
@@ -184,10 +194,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
     const INFCL_LDS float* lp = lcur + 16 * kh + 8 * h;
     const f32x4 L0 = *(const INFCL_LDS f32x4*)lp;
     const f32x4 L1 = *(const INFCL_LDS f32x4*)(lp + 4);
-    const int64_t j0 = (int64_t)jt * kBwdBN;
-    const bool special = (j0 == own0) || (j0 + kBwdBN > b) || !wave_rows_ok;
-    float ds_tile = 0.f;
-    bf16x8 ga;
+    float ds_tile = 0.f, x[8], gv[8];
     const u32x4 drs = tile_rsrc(dtile);
     const uint32_t dlo = dma_lo();
 #pragma unroll
@@ -199,26 +206,32 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
         // offset: only the first instruction follows the lane offset's
         // arithmetic closely enough to need the full padding
         if (kk == 0)
-          dma16_asm(drs, ddst + 1024 * wave, dlo, sweep_dma_kk_off(0, wave, ROWG));
+          dma16_asm(drs, ddst + 1024 * wave, dlo);
         else if (kk < NIW)
-          dma16_asm_w1(drs, ddst + 1024 * (wave + 4 * kk), dlo, sweep_dma_kk_off(kk, wave, ROWG));
+          dma16_asm_w1(drs, ddst + 1024 * (wave + 4 * kk), dlo, sweep_dma_kk_off(kk, 0, ROWG));
       }
-      const float x = mine[i] + (i < 4 ? q0[i] : q1[i - 4]);
-      const float Lj = i < 4 ? L0[i] : L1[i - 4];
-      const float pO = exp2_hw(__builtin_fmaf(x, k2, -aO));
-      const float pS = exp2_hw(__builtin_fmaf(x, k2, -Lj));
-      float gg = pO + pS;
-      float dsv = pO * (x - uO);
-      if (special) {
-        const int64_t j = j0 + 16 * kh + 8 * h + i;
-        const bool ok = (bool)(own_ok & (j < b));
-        const bool dg = j == iown;
-        gg = dg ? gdiag : (ok ? gg : 0.f);
-        dsv = (ok & !dg) ? dsv : 0.f;
-      }
-      ds_tile += dsv;
-      ga[i] = to16<F16>(F16 ? gg * g16a : gg);
+      x[i] = mine[i] + (i < 4 ? q0[i] : q1[i - 4]);
+      gv[i] = gp_entry(x[i], i < 4 ? L0[i] : L1[i - 4], ds_tile);
     }
+    const int j0 = jt * kBwdBN;
+    if ((j0 == own0_t) || (j0 + kBwdBN > rows)) {
+      // tile on the diagonal or past the end: masked entries
+      ds_tile = 0.f;
+      const int lo = opaque_lane();
+      const int jl = j0 + 16 * kh + 8 * (lo >> 5), iown_t = own0_t + (lo & 31);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float dsv = 0.f;
+        const float gg = gp_entry(x[i], i < 4 ? L0[i] : L1[i - 4], dsv);
+        const bool ok = jl + i < rows;
+        const bool dg = jl + i == iown_t;
+        gv[i] = ok ? (dg ? gdiag * (F16 ? g16a : 1.0f) : gg) : 0.f;
+        ds_tile += (ok & !dg) ? dsv : 0.f;
+      }
+    }
+    bf16x8 ga;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ga[i] = to16<F16>(gv[i]);
     const int row = 32 * ob + l32;
     *(INFCL_LDS bf16x8*)(gp + gp_chunk_off(row, 2 * kh + h)) = ga;
     return ds_tile;
@@ -265,7 +278,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   // nxt during GEMM1
   auto body = [&](int jt, const INFCL_LDS char* cur, const INFCL_LDS float* lcur, INFCL_LDS char* nxt,
                   INFCL_LDS float* lnxt) {
-    const int dtile = jt + 1 < ntile ? jt + 1 : -1;
+    const int dtile = jt + 1;  // past the end: a resource of zero bytes
     const f32x16 sacc = gemm1(cur, dtile, lnxt);
     ds_acc += (double)join_gp(jt, lcur, sacc, dtile, nxt);
     __syncthreads();  // the G' block is complete
@@ -277,7 +290,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
     const u32x4 rs = tile_rsrc(0);
     const uint32_t lo = dma_lo();
 #pragma unroll
-    for (int kk = 0; kk < NIW; ++kk) dma16_asm(rs, tA + 1024 * (wave + 4 * kk), lo + sweep_dma_kk_off(kk, wave, ROWG));
+    for (int kk = 0; kk < NIW; ++kk) dma16_asm(rs, tA + 1024 * (wave + 4 * kk), lo, sweep_dma_kk_off(kk, 0, ROWG));
     dma16_asm(lse_rsrc(0), lA, lse_lane_off());
   }
   wait_dma();
@@ -289,23 +302,37 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
     body(jt, odd ? tB : tA, odd ? lB : lA, odd ? tA : tB, odd ? lA : lB);
   }
 
-  // ---- write dOwn: accumulator dacc[o2 FBW + fbw] lane holds feature l32 of
-  // block (wave FBW + fbw), rows 8(r>>2) + 4h + (r&3) of own block o2
+  // ---- write dOwn (or this part's unscaled sums): accumulator
+  // dacc[o2 FBW + fbw] lane holds feature l32 of block (wave FBW + fbw), rows
+  // 8(r>>2) + 4h + (r&3) of own block o2
   const bool all_ok = wg0 + kWideBM <= p.own_end;
+  const int f0 = 32 * (wave * FBW) + l32;
+  if (task.part) {
 #pragma unroll
-  for (int o2 = 0; o2 < 2; ++o2) {
-    auto* dst = (typename GO::type*)p.dOwn + (wg0 - p.own_off + 32 * o2 + 4 * h) * D + 32 * (wave * FBW) + l32;
+    for (int o2 = 0; o2 < 2; ++o2) {
+      float* dst = task.part + (32 * o2 + 4 * h) * D + f0;
 #pragma unroll
-    for (int fbw = 0; fbw < FBW; ++fbw)
+      for (int fbw = 0; fbw < FBW; ++fbw)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = wg0 + 32 * o2 + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (all_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[o2 * FBW + fbw][r]);
-      }
+        for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = dacc[o2 * FBW + fbw][r];
+    }
+  } else {
+#pragma unroll
+    for (int o2 = 0; o2 < 2; ++o2) {
+      auto* dst = (typename GO::type*)sd.dOwn + (wg0 - p.own_off + 32 * o2 + 4 * h) * D + f0;
+#pragma unroll
+      for (int fbw = 0; fbw < FBW; ++fbw)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int64_t row = wg0 + 32 * o2 + 8 * (r >> 2) + 4 * h + (r & 3);
+          if (all_ok || row < p.own_end)
+            dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[o2 * FBW + fbw][r]);
+        }
+    }
   }
 
   // ---- dscale partial of this workgroup: fixed-order reduction
-  red[threadIdx.x] = ds_acc;
+  red[threadIdx.x] = own_ok ? ds_acc : 0.0;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
@@ -372,13 +399,17 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   const int ob = wave >> 1, kh = wave & 1;
   const int l32 = lane & 31, h = lane >> 5;
   const int64_t b = p.b;
-  const int64_t wg0 = p.own_off + (int64_t)blockIdx.x * kWideBM;
+  const BwdTask task = bwd_task(p, kWideBM * D);
+  const BwdSide& sd = p.side[task.sd];
+  const char* const swept = (const char*)sd.swept + (int64_t)task.row0 * ROWG;
+  const float* const lse2_swept = sd.lse2_swept + task.row0;
+  const int rows = task.rows, ntile = (rows + kBwdBN - 1) / kBwdBN;
+  const int64_t wg0 = p.own_off + (int64_t)task.rb * kWideBM;  // own_off is a multiple of 32
   const int64_t own0 = wg0 + 32 * ob;
   const int64_t iown = own0 + l32;
   const bool own_ok = iown < p.own_end;
   const int64_t irow = own_ok ? iown : p.own_end - 1;
-  const bool wave_rows_ok = own0 + 32 <= p.own_end;
-  const int ntile = (int)((b + kBwdBN - 1) / kBwdBN);
+  const int own0_t = (int)(own0 - task.row0);  // counted from the first swept row
 
   const float s = p.scale[0];
   const float k2 = s * kLog2e;
@@ -388,18 +419,20 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
 
   bf16x8 ownf[KH];
   {
-    const __bf16* src = (const __bf16*)p.own + irow * D + kh * (D / 2) + 8 * h;
+    const __bf16* src = (const __bf16*)sd.own + irow * D + kh * (D / 2) + 8 * h;
 #pragma unroll
     for (int s2 = 0; s2 < KH; ++s2) ownf[s2] = *(const bf16x8*)(src + 16 * s2);
   }
-  const float aO = own_ok ? p.lse_own[iown] * kLog2e : 0.f;
+  const float aO = own_ok ? sd.lse_own[iown] * kLog2e : 0.f;
   const float uO = own_ok ? p.udiag[iown] : 0.f;
-  const float gdiag = own_ok ? expm1f(-p.ell_own[iown]) + expm1f(-p.ell_swept[iown]) : 0.f;
+  const float gdiag = own_ok ? expm1f(-sd.ell_own[iown]) + expm1f(-sd.ell_swept[iown]) : 0.f;
 
   // Per-lane address parts, computed once: the kernel has registers to spare
   // at d = 768, and rebuilding them per tile costs several hundred VALU
   // cycles in phases without MFMAs.
-  const uint32_t dma_lo = sweep_dma_lane_off(lane, wave, ROWG);
+  // (the DMA offset of instruction kk: the wave's 4 rows, kept in the lane
+  // part, plus a compile-time constant, the scalar operand)
+  const uint32_t dma_lo = sweep_dma_lane_off(lane, wave, ROWG) + 4 * wave * ROWG;
   // GEMM1's swept fragments: tile base + kSeg (n >> 3) + offA[n & 7].  The
   // kh = 1 wave loads the tile's rows 16..31 into MFMA rows 0..15 and rows
   // 0..15 into 16..31 (row index XOR 16; the row does not enter the bank of
@@ -423,8 +456,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
     for (int s2 = 0; s2 < 2; ++s2) offG[s2] = gp_chunk_off(l32, 2 * s2 + h);
   }
   auto tile_rsrc = [&](int jt) {
-    const int64_t j0 = (int64_t)(jt < 0 ? 0 : jt) * kBwdBN;
-    return rsrc_words((const char*)p.swept + j0 * ROWG, jt < 0 ? 0 : (b - j0) * ROWG);
+    return sweep_tile_rsrc(swept + (int64_t)jt * TILEB, rows - jt * kBwdBN, ROWG);
   };
   auto tbuf = [&](int t) { return tiles + TILEB * (t % 3); };
   // The fragment addresses of GEMM1 in the buffer stage 1 reads next (pA)
@@ -460,23 +492,21 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   };
   // DMA instruction kk of tile jt into its buffer
   auto dma_part = [&](int jt, int kk) {
-    dma16_asm(tile_rsrc(jt < ntile ? jt : -1), tbuf(jt) + 1024 * (wave + 4 * kk),
-              dma_lo + sweep_dma_kk_off(kk, wave, ROWG));
+    dma16_asm(tile_rsrc(jt), tbuf(jt) + 1024 * (wave + 4 * kk), dma_lo, sweep_dma_kk_off(kk, 0, ROWG));
   };
   auto dma_part_w1 = [&](int jt, int kk) {
-    dma16_asm_w1(tile_rsrc(jt < ntile ? jt : -1), tbuf(jt) + 1024 * (wave + 4 * kk),
-                 dma_lo + sweep_dma_kk_off(kk, wave, ROWG));
+    dma16_asm_w1(tile_rsrc(jt), tbuf(jt) + 1024 * (wave + 4 * kk), dma_lo, sweep_dma_kk_off(kk, 0, ROWG));
   };
   // The log-sum-exp values of the 8 swept rows 16 kh + 8 h + i of tile jt
   // whose G' entries the lane forms go straight into registers, one tile
   // ahead (range-checked buffer loads: zeros past b).  Through an LDS slot
   // that every wave filled by DMA the backward took 1% longer.
   auto load_L = [&](int jt, f32x4& A, f32x4& B) {
-    const int64_t j0 = (int64_t)jt * kBwdBN;
-    const bool in = jt < ntile;
-    const int64_t rem = in ? (b - j0) * 4 : 0;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(p.lse2_swept + (in ? j0 : 0)), (short)0, (int)(rem < 128 ? rem : 128), 0x00020000);
+    const int j0 = jt * kBwdBN;
+    int n = rows - j0 < kBwdBN ? rows - j0 : kBwdBN;
+    asm("" : "+s"(n));  // (scalar clamp, as in sweep_tile_rsrc)
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(lse2_swept + j0), (short)0, n > 0 ? 4 * n : 0, 0x00020000);
     const int vo = 4 * (16 * kh + 8 * h);
     A = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, vo, 0, 0));
     B = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, vo + 16, 0, 0));
@@ -596,19 +626,22 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
       const f32x4 L0 = Lc0, L1 = Lc1;
       float gv[8], ds_t = 0.f;
       const f32x16 sacc = stage1(x, L0, L1, gv, ds_t, true);
-      const int64_t j0 = (int64_t)t * kBwdBN;
-      if ((j0 == own0) || (j0 + kBwdBN > b) || !wave_rows_ok) {
+      const int j0 = t * kBwdBN;
+      if ((j0 == own0_t) || (j0 + kBwdBN > rows)) {
         // tile on the diagonal or past the ragged end: masked entries
         ds_t = 0.f;
+        int lo = lane;  // opaque: nothing of the masks is kept across the sweep
+        asm volatile("" : "+v"(lo));
+        const int jl = j0 + 16 * kh + 8 * (lo >> 5), iown_t = own0_t + (lo & 31);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const int64_t j = j0 + 16 * kh + 8 * h + i;
+          const int j = jl + i;
           const float Lj = i < 4 ? L0[i] : L1[i - 4];
           float dsv = 0.f;
           float gg = gp_entry(x[i], Lj, dsv);
-          const bool ok = (bool)(own_ok & (j < b));
-          const bool dg = j == iown;
-          gg = dg ? gdiag * (F16 ? g16a : 1.0f) : (ok ? gg : 0.f);
+          const bool ok = j < rows;
+          const bool dg = j == iown_t;
+          gg = ok ? (dg ? gdiag * (F16 ? g16a : 1.0f) : gg) : 0.f;
           ds_t += (ok & !dg) ? dsv : 0.f;
           gv[i] = gg;
         }
@@ -645,21 +678,34 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
 
   // ---- write dOwn (as bwd_wide)
   const bool all_ok = wg0 + kWideBM <= p.own_end;
+  const int f0 = 32 * (wave * FBW) + l32;
+  if (task.part) {
 #pragma unroll
-  for (int o2 = 0; o2 < 2; ++o2) {
-    auto* dst = (typename GO::type*)p.dOwn + (wg0 - p.own_off + 32 * o2 + 4 * h) * D + 32 * (wave * FBW) + l32;
+    for (int o2 = 0; o2 < 2; ++o2) {
+      float* dst = task.part + (32 * o2 + 4 * h) * D + f0;
 #pragma unroll
-    for (int fbw = 0; fbw < FBW; ++fbw)
+      for (int fbw = 0; fbw < FBW; ++fbw)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = wg0 + 32 * o2 + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (all_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[o2 * FBW + fbw][r]);
-      }
+        for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = dacc[o2 * FBW + fbw][r];
+    }
+  } else {
+#pragma unroll
+    for (int o2 = 0; o2 < 2; ++o2) {
+      auto* dst = (typename GO::type*)sd.dOwn + (wg0 - p.own_off + 32 * o2 + 4 * h) * D + f0;
+#pragma unroll
+      for (int fbw = 0; fbw < FBW; ++fbw)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int64_t row = wg0 + 32 * o2 + 8 * (r >> 2) + 4 * h + (r & 3);
+          if (all_ok || row < p.own_end)
+            dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[o2 * FBW + fbw][r]);
+        }
+    }
   }
 
   // ---- dscale partial: fixed-order reduction in the (now free) join area
   double* red = (double*)&xs_[0][0][0];
-  red[threadIdx.x] = ds_acc;
+  red[threadIdx.x] = own_ok ? ds_acc : 0.0;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
@@ -669,8 +715,6 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
 }
 
 bool bwd_wide_supported(int64_t d, int dtype) { return (dtype == 0 || dtype == 2) && (d == 768 || d == 1024); }
-
-int bwd_wide_workgroups(int64_t nown) { return (int)((nown + kWideBM - 1) / kWideBM); }
 
 int launch_bwd_wide(const BwdParams& p, int nwg, bool f16, hipStream_t stream) {
   auto go = [&](auto f16c, auto g16c) {

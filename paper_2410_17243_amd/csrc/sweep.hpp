@@ -43,6 +43,23 @@ __host__ __device__ __forceinline__ uint32_t sweep_dma_kk_off(int kk, int wave, 
   return (uint32_t)(4 * (k & 7) * rowg + 256 * (k >> 3));
 }
 
+// Resource of one swept tile: `rem` rows of rowg bytes are left from base on
+// (rem <= 0: none; loads past the end give zeros).  Scalar arithmetic only: a
+// clamp of 64-bit byte counts, or a min and max the compiler fuses, would run
+// on the vector unit.
+__device__ __forceinline__ u32x4 sweep_tile_rsrc(const void* base, int rem, int rowg) {
+  int n = rem > kSweepBN ? kSweepBN : rem;
+  asm("" : "+s"(n));
+  n = n < 0 ? 0 : n;
+  const uint64_t a = (uint64_t)base;
+  u32x4 r;
+  r[0] = (uint32_t)a;
+  r[1] = (uint32_t)(a >> 32) & 0xFFFFu;  // stride 0
+  r[2] = (uint32_t)(n * rowg);           // num_records (bytes)
+  r[3] = 0x00020000u;
+  return r;
+}
+
 // Chunk c (0..15) of row r within its segment: the part of the layout's
 // address below the segment base.
 __host__ __device__ __forceinline__ int sweep_seg_off(int r, int c) { return r * kSegRow + 16 * (c ^ sweep_g(r)); }
