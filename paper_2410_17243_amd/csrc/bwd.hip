@@ -49,7 +49,7 @@ constexpr int kGpBytes = kBwdBM * kBwdBN * 2;  // one 16-bit G' exchange buffer
 #define INFCL_BWD_G1_PRE 4
 #endif
 
-template <typename TIN, int D, int FB, bool PIPE, bool G16>
+template <typename TIN, int D, int FB, bool G16>
 __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   constexpr int ES = sizeof(TIN);
   constexpr bool F16 = std::is_same<TIN, _Float16>::value;  // fp16 (else bf16) when ES == 2
@@ -62,8 +62,9 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   constexpr int FBW = ES == 2 ? FB / 4 : FB;  // 32-feature blocks per wave and pass
   constexpr int NACC = ES == 2 ? 4 * FBW : FB;
   constexpr int NPASS = D / (32 * FB);
-  constexpr int GPN = ES == 2 ? (PIPE ? 2 : 1) : 0;  // G' exchange buffers
-  static_assert(!PIPE || ES == 2, "the pipelined schedule is for 16-bit inputs only");
+  constexpr bool PIPE = ES == 2;  // the pipelined schedule
+  static_assert(ES == 4 || NPASS == 1, "16-bit inputs: one pass");
+  constexpr int GPN = PIPE ? 2 : 0;  // G' exchange buffers
   static_assert(D % (32 * FB) == 0, "pass width must divide d");
   static_assert(ES == 4 || FB % 4 == 0, "16-bit pass width is a multiple of 128 features");
   static_assert(D % 64 == 0 && KS % NIW == 0, "tile DMA layout");
@@ -219,9 +220,9 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       __builtin_amdgcn_sched_group_barrier(0x100, kPre, 0);
 #pragma unroll
       for (int s2 = 0; s2 < KS; ++s2) {
-        // one pass: no leading padding (its sources are LDS loads and the own
+        // no leading padding (its sources are LDS loads and the own
         // rows, never restored just before; the build's scan checks it)
-        mfma16_vgpr<F16, (NPASS > 1)>(sacc, ring[s2 % kPre], ownf[s2][0], s2 == 0, s2 == KS - 1);
+        mfma16_vgpr<F16, false>(sacc, ring[s2 % kPre], ownf[s2][0], s2 == 0, s2 == KS - 1);
         dma_step(s2);
         if (s2 + kPre < KS) {
           const int n = s2 + kPre;
@@ -301,9 +302,8 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       *(INFCL_LDS bf16x8*)(gpb + gp_chunk_off(row, 2 * s2 + (lo >> 5))) = ga[s2];
   };
 
-  // GEMM2's per-lane offsets, computed once where the sweep makes one pass
-  // (its feature blocks are then fixed): another 2.5% at d = 512
-  constexpr bool HB = ES == 2 && NPASS == 1;
+  // 16-bit: GEMM2's per-lane offsets, computed once: another 2.5% at d = 512
+  constexpr bool HB = ES == 2;
   int offBh[2][FBW], offGh[2];
   if constexpr (HB) {
 #pragma unroll
@@ -326,10 +326,10 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
     // ---- 16-bit GEMM2 of the tile in cur with the G' in gpb, as an explicit
     // software pipeline over its 2 FBW groups (contraction half s2, feature
     // block fbw; 4 MFMAs each, one per own block): stage g issues the LDS reads
-    // of group g + 2 and then the MFMAs of group g.  With epi the stages also
+    // of group g + 2 and then the MFMAs of group g.  The stages also
     // compute the G' of the next tile (sacc, log-sum-exp values in lnext), a
     // share per stage, into ga.  The stages are separate scheduling regions.
-    auto gemm2_staged = [&](bool epi, const INFCL_LDS char* cur, const INFCL_LDS char* gpb,
+    auto gemm2_staged = [&](const INFCL_LDS char* cur, const INFCL_LDS char* gpb,
                             const INFCL_LDS float* lnext, const f32x16& sacc, bf16x8 (&ga)[2]) -> float {
       constexpr int NG = 2 * FBW;
       constexpr int PD = 2;
@@ -343,17 +343,14 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       auto readA = [&](int s2, bf16x8 (&A)[4]) {
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob)
-          A[ob] = *(const INFCL_LDS bf16x8*)(gpb + 2048 * ob + (HB ? offGh[s2] : gp_chunk_off(lo & 31, 2 * s2 + ho)));
+          A[ob] = *(const INFCL_LDS bf16x8*)(gpb + 2048 * ob + offGh[s2]);
       };
       auto readB = [&](int g, s16x4 (&bq)[2]) {
         const int s2 = g / FBW, fbw = g % FBW;
-        const int fbabs = pass * FB + wave * FBW + fbw;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const int off = HB ? offBh[t][fbw] + 16 * s2 * kSegRow
-                             : sweep_tr_off(lo, t, fbabs) + 16 * kSegRow * s2;
-          bq[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((INFCL_LDS s16x4*)(cur + off));
-        }
+        for (int t = 0; t < 2; ++t)
+          bq[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (INFCL_LDS s16x4*)(cur + offBh[t][fbw] + 16 * s2 * kSegRow));
       };
       // A holds G' of contraction half 0 until the last stage of that half has
       // issued its MFMAs, then half 1 (read straight after).
@@ -361,11 +358,9 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       s16x4 Bq[PD + 1][2];
       f32x4 Lq[NL];
       readA(0, A);
-      if (epi) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (first_stage(q) == 0) Lq[q % NL] = readL(q);
-      }
+      for (int q = 0; q < 4; ++q)
+        if (first_stage(q) == 0) Lq[q % NL] = readL(q);
 #pragma unroll
       for (int g = 0; g < PD && g < NG; ++g) readB(g, Bq[g]);
       __builtin_amdgcn_sched_barrier(0);
@@ -373,20 +368,18 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         if (g + PD < NG) readB(g + PD, Bq[(g + PD) % (PD + 1)]);
-        if (epi) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (first_stage(q) == g + 1) Lq[q % NL] = readL(q);
+        for (int q = 0; q < 4; ++q)
+          if (first_stage(q) == g + 1) Lq[q % NL] = readL(q);
 #pragma unroll
-          for (int i = 0; i < EPS; ++i) {
-            const int r = g * EPS + i;
-            if (r < 16) {
-              const float x = sacc[r];
-              const float pO = exp2_hw(__builtin_fmaf(x, k2, -aO));
-              const float pS = exp2_hw(__builtin_fmaf(x, k2, -Lq[(r >> 2) % NL][r & 3]));
-              ga[r >> 3][r & 7] = to16<F16>(F16 ? (pO + pS) * g16a : pO + pS);
-              ds_tile = __builtin_fmaf(pO, x - uO, ds_tile);
-            }
+        for (int i = 0; i < EPS; ++i) {
+          const int r = g * EPS + i;
+          if (r < 16) {
+            const float x = sacc[r];
+            const float pO = exp2_hw(__builtin_fmaf(x, k2, -aO));
+            const float pS = exp2_hw(__builtin_fmaf(x, k2, -Lq[(r >> 2) % NL][r & 3]));
+            ga[r >> 3][r & 7] = to16<F16>(F16 ? (pO + pS) * g16a : pO + pS);
+            ds_tile = __builtin_fmaf(pO, x - uO, ds_tile);
           }
         }
         const int fbw = g % FBW;
@@ -443,7 +436,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         const f32x16 sacc = gemm1(nxt, true, jt + 2, fre, lfre);
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 ga[2];
-        float dn = gemm2_staged(true, cur, gp + (jt & 1) * kGpBytes, lnxt, sacc, ga);
+        float dn = gemm2_staged(cur, gp + (jt & 1) * kGpBytes, lnxt, sacc, ga);
         // pin the unmasked G' here: otherwise it is sunk into the not-special
         // branch below and computed after GEMM2 instead of alongside it
         asm volatile("" : "+v"(ga[0]), "+v"(ga[1]), "+v"(dn));
@@ -466,7 +459,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         body(jt + 2, tC, tA, lA, tB, lB);
       }
     } else {
-      // Two tile buffers: GEMM1 of tile jt (issuing the loads of tile jt+1),
+      // fp32: two tile buffers, GEMM1 of tile jt (issuing the loads of tile jt+1),
       // G', GEMM2.
       issue_tile(0, tA, lA);
       wait_dma();
@@ -477,15 +470,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         float gv[16];
         const float d0 = epilogue(jt, lcur, sacc, gv);
         if (pass == 0) ds_acc += (double)d0;
-        if constexpr (ES == 2) {
-          bf16x8 ga[2];
-          to_h16(gv, ga);
-          put_gp(gp, ga);
-          __syncthreads();
-          gemm2_staged(false, cur, gp, lcur, sacc, ga);
-        } else {
-          gemm2_f32(cur, gv);
-        }
+        gemm2_f32(cur, gv);
         wait_dma();
         __syncthreads();
       };
@@ -617,16 +602,11 @@ __global__ void __launch_bounds__(256) dscale_finish(const double* part, int64_t
 // Pass width: largest FB (32-feature blocks) dividing d/32 whose accumulators
 // (16 FB registers) fit next to the own operand (d/4 or d/2 registers); for
 // 16-bit inputs FB is also a multiple of 4 (see the transposing-read addressing).
-// Build-time tuning knobs: the register budget shared by the own operand and
-// the gradient accumulators, and whether the three-buffer pipeline is used
-// (16-bit widths whose three tiles fit in LDS).
+// Build-time tuning knob: the register budget shared by the own operand and
+// the gradient accumulators.
 #ifndef INFCL_BWD_REG_BUDGET
 #define INFCL_BWD_REG_BUDGET 384
 #endif
-#ifndef INFCL_BWD_PIPE
-#define INFCL_BWD_PIPE 1
-#endif
-
 template <typename TIN, int D>
 static int launch_bwd_d(const BwdParams& p, int nwg, hipStream_t stream) {
   constexpr int ES = sizeof(TIN);
@@ -640,15 +620,13 @@ static int launch_bwd_d(const BwdParams& p, int nwg, hipStream_t stream) {
     return best;
   }();
   static_assert(ES == 4 || FB % 4 == 0, "16-bit pass width must be a multiple of 128 features");
-  constexpr int TILEB = kBwdBN * D * ES;
-  constexpr bool PIPE = INFCL_BWD_PIPE != 0 && ES == 2 && 3 * (TILEB + 128) + 2 * kGpBytes + 2048 <= 160 * 1024;
   if constexpr (ES == 2) {
     if (p.gdt) {
-      hipLaunchKernelGGL((bwd_sweep<TIN, D, FB, PIPE, true>), dim3(nwg), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((bwd_sweep<TIN, D, FB, true>), dim3(nwg), dim3(256), 0, stream, p);
       return hipGetLastError() == hipSuccess ? 0 : 1;
     }
   }
-  hipLaunchKernelGGL((bwd_sweep<TIN, D, FB, PIPE, false>), dim3(nwg), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((bwd_sweep<TIN, D, FB, false>), dim3(nwg), dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
@@ -661,9 +639,7 @@ static int launch_bwd_t(const BwdParams& p, int nwg, hipStream_t stream) {
       case 256: return launch_bwd_d<TIN, 256>(p, nwg, stream);
       case 384: return launch_bwd_d<TIN, 384>(p, nwg, stream);
       case 512: return launch_bwd_d<TIN, 512>(p, nwg, stream);
-      case 640: return launch_bwd_d<TIN, 640>(p, nwg, stream);
-      case 896: return launch_bwd_d<TIN, 896>(p, nwg, stream);
-      // 768 and 1024 take the single-pass wide-row sweep
+      // wider rows take the wide-row sweep
     }
   } else {
     switch (d) {
@@ -801,7 +777,7 @@ BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
   return pl;
 }
 
-// Backward: 16-bit inputs with d = 768 or 1024 take the single-pass wide-row sweep
+// Backward: 16-bit inputs with d >= 640 take the single-pass wide-row sweep
 // (64 own rows per workgroup), everything else the 128-row sweep above.  Own
 // rows are [r0, r0 + nrows) of both sides (all b for the whole batch; a
 // shard's samples otherwise, with dimg/dtxt [nrows, d]: fp32, or with gdt = 1

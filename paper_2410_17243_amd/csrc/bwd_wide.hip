@@ -1,15 +1,18 @@
-// Backward sweep for wide rows (16-bit inputs: bf16 or fp16, d = 768 or
-// 1024) in a single pass (gfx950): bwd_wide below, the serial form, serves
-// d = 1024; bwd_wide3 further down, the pipelined form, serves d = 768.
+// Backward sweep for wide rows (16-bit inputs: bf16 or fp16, d = 640 to 1024)
+// in a single pass (gfx950): bwd_wide below, the serial form, serves d = 896
+// and 1024; bwd_wide3 further down, the pipelined form, d = 640 and 768 (three
+// of its tiles fit in LDS).
 //
 // Same quantities as the 128-row sweep (Sec. 3.1, Eq. 6-8 completed for both
 // halves of the loss and the scale; the appendix's in-GPU backward recomputes
 // every tile from the saved log-sum-exp vectors).  At these widths the
 // gradient accumulators of 128 own rows (128 x d fp32) do not fit the
-// register file, so a workgroup owns 64 rows instead: 64 x d fp32 is 192 or
-// 256 AGPRs per wave.  GEMM1's own operand is then split by contraction: the
-// wave pair (2 ob, 2 ob + 1) holds own block ob (32 rows), each wave one half
-// of the features (d/8 VGPRs), and computes a partial S^T block over its half.
+// register file, so a workgroup owns 64 rows instead: 64 x d fp32 is d/4
+// AGPRs per wave.  (The 128-row sweep in passes of 128 features, each
+// recomputing GEMM1, took 5.8 ms per side at b = 10007, d = 640, before both
+// this form and the split of row blocks; this form 0.44 ms for both sides.)  GEMM1's own operand is then split by contraction: the
+// wave pair (2 ob, 2 ob + 1) holds own block ob (32 rows), each wave every
+// other 16-feature step (d/8 VGPRs), and computes a partial S^T block over its half.
 // Per tile:
 //   GEMM1   partial S^T (32 swept x 32 own) over the wave's feature half
 //           (and the DMA of the next tile's log-sum-exp slot);
@@ -38,13 +41,13 @@ template <int D, bool F16, bool G16>
 __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   using GO = GradOut<G16, F16>;  // gradient element type
   constexpr int KS = D / 16;  // 16-wide contraction steps of the full width
-  constexpr int KH = KS / 2;  // steps of one wave (half the features)
+  constexpr int KH = KS / 2;  // steps of one wave: the even steps, or the odd ones
   constexpr int ROWG = D * 2;
   constexpr int TILEB = kBwdBN * ROWG;
   constexpr int NIW = TILEB / 4096;  // 1 KiB DMA instructions per wave and tile
   constexpr int FBW = D / 128;       // 32-feature blocks of GEMM2 per wave
   constexpr int kPre = 4;
-  static_assert(KH % 8 == 0, "feature halves start on a 128-feature segment");
+  static_assert(KH % 4 == 0, "four steps of a wave per 128-feature segment");
   static_assert(2 * TILEB + 2 * 1024 + kWideBM * kBwdBN * 2 + 4 * 64 * 32 + 2048 <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char tA_[TILEB];
   __shared__ __attribute__((aligned(1024))) char tB_[TILEB];
@@ -86,12 +89,12 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   const float g16a = F16 ? p.g16[0] : 1.0f;
   const float kfin = dl * s / (2.0f * (float)b) * (F16 ? p.g16[1] : 1.0f);
 
-  // own operand of GEMM1: row irow, features kh d/2 + 16 s2 + 8h .. +8
+  // own operand of GEMM1: row irow, features 16 (2 s2 + kh) + 8h .. +8
   bf16x8 ownf[KH];
   {
-    const __bf16* src = (const __bf16*)sd.own + irow * D + kh * (D / 2) + 8 * h;
+    const __bf16* src = (const __bf16*)sd.own + irow * D + 16 * kh + 8 * h;
 #pragma unroll
-    for (int s2 = 0; s2 < KH; ++s2) ownf[s2] = *(const bf16x8*)(src + 16 * s2);
+    for (int s2 = 0; s2 < KH; ++s2) ownf[s2] = *(const bf16x8*)(src + 32 * s2);
   }
   const float aO = own_ok ? sd.lse_own[iown] * kLog2e : 0.f;
   const float uO = own_ok ? p.udiag[iown] : 0.f;
@@ -119,10 +122,10 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   // rows 0..15 into 16..31 (row index XOR 16; the row does not enter the bank
   // of a chunk): accumulator entries 0..7 of either wave are then the ones it
   // finishes (tile rows 16 kh + 8 h + i), entries 8..15 the ones it hands over.
-  auto make_offA = [&](int lo, int (&o)[8]) {
+  auto make_offA = [&](int lo, int (&o)[4]) {
     const int rA = sweep_perm(lo & 31) ^ (16 * kh);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) o[k] = sweep_seg_off(rA, 2 * k + (lo >> 5));
+    for (int k = 0; k < 4; ++k) o[k] = sweep_seg_off(rA, 2 * (2 * k + kh) + (lo >> 5));
   };
   // GEMM2's transposing reads (tile base + offB[t][fbw] + 16 kSegRow s2) and
   // G' fragments (G' block + offG[s2])
@@ -145,14 +148,13 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   // ---- GEMM1 over this wave's feature half of the tile in cur; issues the
   // DMA of tile dtile's log-sum-exp slot
   auto gemm1 = [&](const INFCL_LDS char* cur, int dtile, INFCL_LDS float* dlse) {
-    int offA[8];
+    int offA[4];
     make_offA(opaque_lane(), offA);
-    const INFCL_LDS char* half = cur + kSeg * (kh * KH / 8);
     const u32x4 drl = lse_rsrc(dtile);
     f32x16 sacc;
     bf16x8 ring[kPre];
 #pragma unroll
-    for (int i = 0; i < kPre; ++i) ring[i] = *(const INFCL_LDS bf16x8*)(half + offA[i & 7] + kSeg * (i >> 3));
+    for (int i = 0; i < kPre; ++i) ring[i] = *(const INFCL_LDS bf16x8*)(cur + offA[i & 3] + kSeg * (i >> 2));
     __builtin_amdgcn_sched_group_barrier(0x100, kPre, 0);
 #pragma unroll
     for (int s2 = 0; s2 < KH; ++s2) {
@@ -160,7 +162,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
       if (s2 == 1) dma16_asm(drl, dlse, lse_lane_off());
       if (s2 + kPre < KH) {
         const int n = s2 + kPre;
-        ring[s2 % kPre] = *(const INFCL_LDS bf16x8*)(half + offA[n & 7] + kSeg * (n >> 3));
+        ring[s2 % kPre] = *(const INFCL_LDS bf16x8*)(cur + offA[n & 3] + kSeg * (n >> 2));
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
     }
@@ -376,7 +378,7 @@ template <int D, bool F16, bool G16>
 __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   using GO = GradOut<G16, F16>;  // gradient element type
   constexpr int KS = D / 16;
-  constexpr int KH = KS / 2;
+  constexpr int KH = KS / 2;  // as in bwd_wide
   constexpr int ROWG = D * 2;
   constexpr int TILEB = kBwdBN * ROWG;
   constexpr int NIW = TILEB / 4096;  // 1 KiB DMA instructions per wave and tile
@@ -386,7 +388,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
 #endif
   constexpr int kPre = INFCL_W3_PRE;
   constexpr int NG = 2 * FBW;  // GEMM2 groups
-  static_assert(KH % 8 == 0 && KH >= 8, "feature halves start on a 128-feature segment");
+  static_assert(KH % 4 == 0 && KH >= 16, "four steps of a wave per 128-feature segment, two per G' entry");
   static_assert(3 * TILEB + kWideBM * kBwdBN * 2 + 4 * 64 * 8 * 4 <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char tiles_[3 * TILEB];
   __shared__ __attribute__((aligned(1024))) char gp_[kWideBM * kBwdBN * 2];
@@ -419,9 +421,9 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
 
   bf16x8 ownf[KH];
   {
-    const __bf16* src = (const __bf16*)sd.own + irow * D + kh * (D / 2) + 8 * h;
+    const __bf16* src = (const __bf16*)sd.own + irow * D + 16 * kh + 8 * h;
 #pragma unroll
-    for (int s2 = 0; s2 < KH; ++s2) ownf[s2] = *(const bf16x8*)(src + 16 * s2);
+    for (int s2 = 0; s2 < KH; ++s2) ownf[s2] = *(const bf16x8*)(src + 32 * s2);
   }
   const float aO = own_ok ? sd.lse_own[iown] * kLog2e : 0.f;
   const float uO = own_ok ? p.udiag[iown] : 0.f;
@@ -433,17 +435,17 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   // (the DMA offset of instruction kk: the wave's 4 rows, kept in the lane
   // part, plus a compile-time constant, the scalar operand)
   const uint32_t dma_lo = sweep_dma_lane_off(lane, wave, ROWG) + 4 * wave * ROWG;
-  // GEMM1's swept fragments: tile base + kSeg (n >> 3) + offA[n & 7].  The
+  // GEMM1's swept fragments of the wave's step n: tile base + kSeg (n >> 2) + offA[n & 3].  The
   // kh = 1 wave loads the tile's rows 16..31 into MFMA rows 0..15 and rows
   // 0..15 into 16..31 (row index XOR 16; the row does not enter the bank of
   // a chunk, so the reads stay conflict free): then accumulator entries 0..7
   // of either wave are the ones it finishes (tile rows 16 kh + 8 h + i) and
   // entries 8..15 the ones it hands over, with no selection by kh.
-  int offA[8];
+  int offA[4];
   {
     const int rA = sweep_perm(l32) ^ (16 * kh);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) offA[k] = sweep_seg_off(rA, 2 * k + h);
+    for (int k = 0; k < 4; ++k) offA[k] = sweep_seg_off(rA, 2 * (2 * k + kh) + h);
   }
   int offB[2][FBW];  // GEMM2's transposing reads: tile base + offB + 16 kSegRow s2
   int offG[2];       // GEMM2's G' fragments of feature step s2
@@ -463,10 +465,10 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   // and of GEMM2 in the buffer stage 2 reads next (pB), advanced with the
   // buffer rotation before the barrier that ends each iteration, so that no
   // address arithmetic sits between a barrier and the MFMAs after it.
-  const INFCL_LDS char* pA[8];
+  const INFCL_LDS char* pA[4];
   const INFCL_LDS char* pB[2][FBW];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) pA[k] = tbuf(0) + kSeg * (kh * KH / 8) + offA[k];
+  for (int k = 0; k < 4; ++k) pA[k] = tbuf(0) + offA[k];
 #pragma unroll
   for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
@@ -475,7 +477,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   auto advance_pA = [&](int t1) {
     const int delta = rot(t1);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < 4; ++k) {
       pA[k] += delta;
       asm volatile("" : "+v"(pA[k]));
     }
@@ -536,18 +538,18 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
     f32x16 sacc;
     bf16x8 ring[kPre];
 #pragma unroll
-    for (int i = 0; i < kPre; ++i) ring[i] = *(const INFCL_LDS bf16x8*)(pA[i & 7] + kSeg * (i >> 3));
+    for (int i = 0; i < kPre; ++i) ring[i] = *(const INFCL_LDS bf16x8*)(pA[i & 3] + kSeg * (i >> 2));
     __builtin_amdgcn_sched_group_barrier(0x100, kPre, 0);
 #pragma unroll
     for (int s2 = 0; s2 < KH; ++s2) {
       mfma16_vgpr<F16, false>(sacc, ring[s2 % kPre], ownf[s2], s2 == 0, s2 == KH - 1);  // unpadded: scan-checked
       if (s2 + kPre < KH) {
         const int n = s2 + kPre;
-        ring[s2 % kPre] = *(const INFCL_LDS bf16x8*)(pA[n & 7] + kSeg * (n >> 3));
+        ring[s2 % kPre] = *(const INFCL_LDS bf16x8*)(pA[n & 3] + kSeg * (n >> 2));
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      if (with_gp && s2 % 3 == 1) {
-        const int i = s2 / 3;  // 8 entries over the 24 MFMAs
+      const int i = (8 * s2 - 1) / KH;  // entry i after step i KH / 8 + 1: 8 entries spread over the MFMAs
+      if (with_gp && s2 == i * KH / 8 + 1) {
         gv[i] = gp_entry(x[i], i < 4 ? L0[i] : L1[i - 4], ds_t);
         // kept here: the compiler would otherwise move part of the entry's
         // arithmetic past the MFMAs, into the phase after them
@@ -714,20 +716,24 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   if (threadIdx.x == 0) p.ds_part[blockIdx.x] = red[0];
 }
 
-bool bwd_wide_supported(int64_t d, int dtype) { return (dtype == 0 || dtype == 2) && (d == 768 || d == 1024); }
+bool bwd_wide_supported(int64_t d, int dtype) { 
+  return (dtype == 0 || dtype == 2) && (d == 640 || d == 768 || d == 896 || d == 1024);
+}
 
 int launch_bwd_wide(const BwdParams& p, int nwg, bool f16, hipStream_t stream) {
   auto go = [&](auto f16c, auto g16c) {
     constexpr bool F = decltype(f16c)::value, G = decltype(g16c)::value;
-    if (p.d == 768)
-      hipLaunchKernelGGL((bwd_wide3<768, F, G>), dim3(nwg), dim3(256), 0, stream, p);
-    else
-      hipLaunchKernelGGL((bwd_wide<1024, F, G>), dim3(nwg), dim3(256), 0, stream, p);
+    switch (p.d) {
+      case 640: hipLaunchKernelGGL((bwd_wide3<640, F, G>), dim3(nwg), dim3(256), 0, stream, p); break;
+      case 768: hipLaunchKernelGGL((bwd_wide3<768, F, G>), dim3(nwg), dim3(256), 0, stream, p); break;
+      case 896: hipLaunchKernelGGL((bwd_wide<896, F, G>), dim3(nwg), dim3(256), 0, stream, p); break;
+      case 1024: hipLaunchKernelGGL((bwd_wide<1024, F, G>), dim3(nwg), dim3(256), 0, stream, p); break;
+      default: return 2;
+    }
     return hipGetLastError() == hipSuccess ? 0 : 1;
   };
   using T = std::true_type;
   using N = std::false_type;
-  if (p.d != 768 && p.d != 1024) return 2;
   if (f16) return p.gdt ? go(T{}, T{}) : go(T{}, N{});
   return p.gdt ? go(N{}, T{}) : go(N{}, N{});
 }
