@@ -11,17 +11,15 @@
 
 namespace infcl {
 int launch_fwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype, const float* scale, float* loss,
-               double* loss64, float* lse_r, float* lse_c, float* aux, hipStream_t stream, float* rowR, float* rowL,
-               float* colR, float* colL, float* udiag, float* ref2, double* partial);
+               double* loss64, float* lse_r, float* lse_c, float* aux, hipStream_t stream, float* pairs, float* udiag,
+               float* ref2, double* partial);
 int launch_fwd_shard(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
-                     const float* scale, float* colpair, hipStream_t stream, float* rowR, float* rowL, float* colR,
-                     float* colL, float* udiag, float* ref2);
+                     const float* scale, float* colpair, hipStream_t stream, float* pairs, float* udiag, float* ref2);
 int launch_fwd_shard_finish(int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows, int64_t nparts,
                             const float* colpairs, const float* scale, float* lse_r, float* lse_c, float* aux,
-                            double* loss_part, hipStream_t stream, const float* rowR, const float* rowL,
-                            const float* udiag, double* partial);
-void fwd1_grid(int64_t b, int64_t nrows, int* Pr, int* Pc);
-void fwd2_grid(int64_t b, int64_t nrows, int64_t d, int* Pr, int* Pc);
+                            double* loss_part, hipStream_t stream, float* pairs, const float* udiag, double* partial);
+int fwd1_pairs(int64_t b);
+int fwd2_pairs(int64_t b, int64_t d);
 bool fwd2_supported(int64_t d, int dtype);
 int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
                const float* scale, const float* lse_r, const float* lse_c, const float* aux, const float* dloss,
@@ -51,70 +49,87 @@ size_t elem_size(int dtype) { return dtype == INFCL_F32 ? 4 : 2; }
 
 struct Layout {
   int64_t dk;  // the width the sweeps run at
-  size_t lse2, bwd_part, g16, pad, gpad, rowR, rowL, colR, colL, udiag, ref2, fwd_part;
-  size_t fwd_total;  // bytes without the backward's partial sums
+  size_t pad, pairs, udiag, ref2, fwd_part;
+  size_t fwd_total;  // the forward's share, from the start
+  size_t lse2, bwd_part, g16, gpad;
+  size_t part, part_bytes;  // the backward's partial sums
   size_t total;
-  size_t part() const { return rowR; }  // the backward's partial sums take the place of the forward's pairs
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Most bytes of partial gradient sums a backward may use beyond the forward's
-// partial pairs, whose place they take: 256 workgroups x 128 rows x 512
-// features x 4 bytes (or 64 rows x 1024), one part for every compute unit.
+// Most bytes of partial gradient sums a backward may use: 256 workgroups x 128
+// rows x 512 features x 4 bytes (or 64 rows x 1024), one part for every
+// compute unit.
 constexpr size_t kPartBytes = ((size_t)64 << 20) + 4096;
 
-// Workspace regions, sized for the sweeps that (b, d, dtype) launches: the
-// base-2 log-sum-exp vectors of the backward, the dscale partials and fp16's
-// G' scale, the padded copies; then the partial pairs of the forward grid
-// (resident rows: Pc row and Pr column partials per sample; streamed tiles:
-// 4 Pc and Pr), the diagonal, the base-2 diagonal references (resident rows
-// only) and the loss partials.  The backward, which no longer needs what the
-// forward left there, keeps the partial sums of split row blocks in the same
-// place, which is enlarged where a whole batch's split needs more.  A shard
-// of nrows <= b rows needs no more of the forward's regions (its grid has at
-// most as many row groups and its row partials are nrows long) and splits its
-// blocks as far as the place allows.
+// Workspace regions, sized for the sweeps that (b, d, dtype) launches.  The
+// forward's: the padded copies of the inputs, the partial pairs of its grid,
+// the diagonal, the base-2 diagonal references (resident rows only) and the
+// loss partials.  The backward's: the base-2 log-sum-exp vectors, the dscale
+// partials, fp16's G' scale, the padded gradients, and the partial sums of
+// split row blocks; those take the place of the forward's pairs, which the
+// backward no longer needs, enlarged to kPartBytes (or to what the split of
+// so small a batch can use) for batches up to 32768, whose row blocks, or a
+// shard's, leave compute units idle.  A shard uses the same regions: its
+// forward leaves at most as many pairs and it splits its row blocks as far as
+// the place allows.
 Layout make_layout(int64_t b, int64_t d, int dtype) {
   Layout L;
   L.dk = kernel_width(d, dtype);
-  int Pr = 0, Pc = 0;
-  size_t nrow = 0, ncol = 0;
   const bool resident = infcl::fwd2_supported(L.dk, dtype);
-  if (resident) {
-    infcl::fwd2_grid(b, b, L.dk, &Pr, &Pc);
-    nrow = (size_t)Pc;
-  } else {
-    infcl::fwd1_grid(b, b, &Pr, &Pc);
-    nrow = (size_t)Pc * 4;
-  }
-  ncol = (size_t)Pr;
-  size_t off = 0;
+  const size_t npair = (size_t)(resident ? infcl::fwd2_pairs(b, L.dk) : infcl::fwd1_pairs(b));
   const size_t fb = (size_t)b * sizeof(float);
+  size_t off = 0;
+  L.pad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * elem_size(dtype) : 0));  // img, txt
+  L.pairs = off; off = align256(off + 2 * npair * fb + 1024);  // (each of the four arrays is aligned)
+  L.udiag = off; off = align256(off + fb);
+  L.ref2 = off; off = align256(off + (resident ? fb : 0));
+  L.fwd_part = off; off = align256(off + (size_t)((b + 31) / 32) * sizeof(double));
+  L.fwd_total = off;
   L.lse2 = off; off = align256(off + 2 * fb);
   L.bwd_part = off; off = align256(off + (size_t)2 * ((b + 63) / 64) * sizeof(double));  // 64 or 128 rows per WG
   L.g16 = off; off = align256(off + (dtype == INFCL_F16 ? (size_t)(2 + 2 * ((b + 255) / 256)) * sizeof(float) : 0));
-  L.pad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * elem_size(dtype) : 0));  // img, txt
   L.gpad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * sizeof(float) : 0));  // dimg, dtxt
-  L.rowR = off; off = align256(off + nrow * fb);
-  L.rowL = off; off = align256(off + nrow * fb);
-  L.colR = off; off = align256(off + ncol * fb);
-  L.colL = off; off = align256(off + ncol * fb);
-  L.udiag = off; off = align256(off + fb);
-  L.ref2 = off; off = align256(off + (resident ? fb : 0));
-  L.fwd_part = off; off = align256(off + (size_t)((b + 255) / 256) * sizeof(double));
-  L.fwd_total = off;
-  const size_t part = align256(infcl::plan_bwd(b, b, L.dk, dtype, kPartBytes).part_bytes);
-  L.total = L.part() + part > off ? L.part() + part : off;
+  // partial sums: in place of the pairs, or, where those are too few, at the end
+  L.part = L.pairs;
+  L.part_bytes = L.fwd_total - L.pairs;
+  if (L.part_bytes > kPartBytes) L.part_bytes = kPartBytes;
+  size_t want = 0;
+  if (b <= 32768) {
+    const size_t ntile = (size_t)(b + 31) / 32;
+    want = 2 * (size_t)(b + 127) / 128 * 128 * (size_t)L.dk * sizeof(float) * ntile + 4096;  // every tile its part
+    if (want > kPartBytes) want = kPartBytes;
+  } else {
+    want = align256(infcl::plan_bwd(b, b, L.dk, dtype, kPartBytes).part_bytes);
+  }
+  if (want > L.part_bytes) {
+    L.part = off;
+    L.part_bytes = want;
+    off = align256(off + want);
+  }
+  L.total = off;
   return L;
 }
 
-// Bytes of partial sums a backward call may use: what the layout holds there,
-// at most kPartBytes (so that the split, and the bits of the result, follow
-// from the shape alone).
-size_t part_cap(const Layout& L) {
-  const size_t room = L.total - L.part();
-  return room < kPartBytes ? room : kPartBytes;
+// What infcl_fwd_noalloc's fixed scratch is measured by: the workspace of a
+// 32 x 8 (resident rows) or 64 x 8 (streamed) forward grid, both passes'
+// vectors and padded copies.  Never less than the forward's share of the
+// layout near the limit; where the limit lies is part of the interface.
+size_t noalloc_need(int64_t b, int64_t d, int dtype) {
+  const int64_t dk = kernel_width(d, dtype);
+  const bool resident = infcl::fwd2_supported(dk, dtype);
+  const int64_t bm = resident ? (dk > 512 ? 128 : 256) : 64, bn = resident ? 32 : 256, rmax = resident ? 32 : 64;
+  const int64_t nrb = (b + bm - 1) / bm, nct = (b + bn - 1) / bn;
+  const size_t ncol = (size_t)(nrb < rmax ? nrb : rmax), nrow = (size_t)(nct < 8 ? nct : 8) * (resident ? 1 : 4);
+  const size_t fb = (size_t)b * sizeof(float);
+  size_t n = 2 * align256(nrow * fb) + 2 * align256(ncol * fb) + align256(fb) + align256(resident ? fb : 0) +
+             align256((size_t)((b + 255) / 256) * sizeof(double)) + align256(2 * fb) +
+             align256((size_t)2 * ((b + 63) / 64) * sizeof(double));
+  if (dtype == INFCL_F16) n += align256((size_t)(2 + 2 * ((b + 255) / 256)) * sizeof(float));
+  if (dk != d)
+    n += align256(2 * (size_t)b * (size_t)dk * elem_size(dtype)) + align256(2 * (size_t)b * (size_t)dk * sizeof(float));
+  return n;
 }
 
 // Row copy between widths: rows of cin 16-byte chunks into rows of cout
@@ -244,8 +259,7 @@ infcl_status infcl_fwd(const void* img, const void* txt, int64_t b, int64_t d, i
   char* ws = (char*)workspace;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   int rc = infcl::launch_fwd(img, txt, b, L.dk, dtype, scale, loss, loss64, lse_r, lse_c, aux, (hipStream_t)stream,
-                             (float*)(ws + L.rowR), (float*)(ws + L.rowL), (float*)(ws + L.colR),
-                             (float*)(ws + L.colL), (float*)(ws + L.udiag), (float*)(ws + L.ref2),
+                             (float*)(ws + L.pairs), (float*)(ws + L.udiag), (float*)(ws + L.ref2),
                              (double*)(ws + L.fwd_part));
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
 }
@@ -259,13 +273,12 @@ infcl_status infcl_fwd_noalloc(const void* img, const void* txt, int64_t b, int6
   if (loss64 != nullptr && ((uintptr_t)loss64 % 8) != 0) return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype)) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (L.fwd_total > kScratchBytes) return INFCL_ERR_WORKSPACE;
+  if (noalloc_need(b, d, dtype) > kScratchBytes || L.fwd_total > kScratchBytes) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)scratch_address();
   if (ws == nullptr) return INFCL_ERR_HIP;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   int rc = infcl::launch_fwd(img, txt, b, L.dk, dtype, scale, loss, loss64, lse_r, lse_c, aux, (hipStream_t)stream,
-                             (float*)(ws + L.rowR), (float*)(ws + L.rowL), (float*)(ws + L.colR),
-                             (float*)(ws + L.colL), (float*)(ws + L.udiag), (float*)(ws + L.ref2),
+                             (float*)(ws + L.pairs), (float*)(ws + L.udiag), (float*)(ws + L.ref2),
                              (double*)(ws + L.fwd_part));
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
 }
@@ -290,7 +303,7 @@ infcl_status infcl_bwd(const void* img, const void* txt, int64_t b, int64_t d, i
   grad_targets(gi, gt, b, d, ges, ws, L);
   int rc = infcl::launch_bwd(img, txt, b, L.dk, dtype, 0, b, scale, lse_r, lse_c, aux, dloss, gi, gt, gk, dscale,
                              nullptr, (float*)(ws + L.lse2), (double*)(ws + L.bwd_part), (float*)(ws + L.g16),
-                             (float*)(ws + L.part()), part_cap(L), (hipStream_t)stream);
+                             (float*)(ws + L.part), L.part_bytes, (hipStream_t)stream);
   if (rc == 2) return INFCL_ERR_UNSUPPORTED;
   if (rc == 0 && !unstage_grads(dimg, dtxt, b, b, d, ges, ws, L, (hipStream_t)stream)) rc = 1;
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
@@ -311,8 +324,7 @@ infcl_status infcl_fwd_shard(const void* img, const void* txt, int64_t b, int64_
   char* ws = (char*)workspace;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   int rc = infcl::launch_fwd_shard(img, txt, b, L.dk, dtype, r0, bs, scale, colpair, (hipStream_t)stream,
-                                   (float*)(ws + L.rowR), (float*)(ws + L.rowL), (float*)(ws + L.colR),
-                                   (float*)(ws + L.colL), (float*)(ws + L.udiag), (float*)(ws + L.ref2));
+                                   (float*)(ws + L.pairs), (float*)(ws + L.udiag), (float*)(ws + L.ref2));
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
 }
 
@@ -328,9 +340,8 @@ infcl_status infcl_fwd_shard_finish(int64_t b, int64_t d, int dtype, int64_t r0,
   if (ws_bytes < L.total) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   int rc = infcl::launch_fwd_shard_finish(b, L.dk, dtype, r0, bs, nparts, colpairs, scale, lse_r, lse_c, aux, loss_part,
-                                          (hipStream_t)stream, (const float*)(ws + L.rowR),
-                                          (const float*)(ws + L.rowL), (const float*)(ws + L.udiag),
-                                          (double*)(ws + L.fwd_part));
+                                          (hipStream_t)stream, (float*)(ws + L.pairs),
+                                          (const float*)(ws + L.udiag), (double*)(ws + L.fwd_part));
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
 }
 
@@ -355,7 +366,7 @@ infcl_status infcl_bwd_shard(const void* img, const void* txt, int64_t b, int64_
   grad_targets(gi, gt, b, d, ges, ws, L);
   int rc = infcl::launch_bwd(img, txt, b, L.dk, dtype, r0, bs, scale, lse_r, lse_c, aux, dloss, gi, gt, gk, nullptr,
                              dscale_part, (float*)(ws + L.lse2), (double*)(ws + L.bwd_part), (float*)(ws + L.g16),
-                             (float*)(ws + L.part()), part_cap(L), (hipStream_t)stream);
+                             (float*)(ws + L.part), L.part_bytes, (hipStream_t)stream);
   if (rc == 2) return INFCL_ERR_UNSUPPORTED;
   if (rc == 0 && !unstage_grads(dimg, dtxt, bs, b, d, ges, ws, L, (hipStream_t)stream)) rc = 1;
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;

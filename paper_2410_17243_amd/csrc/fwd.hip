@@ -445,33 +445,54 @@ struct FinParams {
   double* partial;     // [gridDim.x]
 };
 
-// natural-log log-sum-exp of n base-2 partial pairs (R, l) at R/L[k stride + t].
-// Both passes keep eight loads in flight (one load per iteration, each waited
-// for, made the merge latency-bound); an empty pair (R = -inf) is weighted by
-// zero.  The sum runs in the same order as a plain loop over k.
-__device__ __forceinline__ double merge_parts(const float* R, const float* L, int n, int64_t stride, int64_t t) {
-  double M = -__builtin_inf();
-#pragma unroll 8
-  for (int k = 0; k < n; ++k) M = fmax(M, (double)R[(int64_t)k * stride + t]);
-  if (M == -__builtin_inf()) return -__builtin_inf();
+// One workgroup finishes 32 samples: thread (t, g) of 32 x 8 takes every eighth
+// partial pair of sample t from pair g on (32 samples' pairs of one slot are
+// one 128-byte line), and the eight parts meet in LDS.  With one thread per
+// sample the 16 to 96 fp64 exponentials of a sample were one serial chain:
+// 12 us at 40 pairs and 21 us at 96 whatever the batch, against 7 and 10 us
+// (25 against 17 us at b = 131072, where it is 1e-4 of the forward).
+constexpr int kFinT = 32, kFinG = 8;
+
+// natural-log log-sum-exp of the n base-2 partial pairs (R, l) of sample t at
+// R/L[k stride + t], in every thread of the sample; an empty pair (R = -inf)
+// weighs zero.  Each thread keeps up to eight pairs in registers.  The order of
+// the additions is fixed by n alone.
+__device__ __forceinline__ double merge_parts(const float* R, const float* L, int n, int64_t stride, int64_t t, bool ok,
+                                              int tl, int g, float (*sm)[kFinT], double (*ss)[kFinT]) {
+  float M = -__builtin_inff();
+  float r[8], l[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int k = g + kFinG * u;
+    const bool in = ok && k < n;
+    r[u] = in ? R[(int64_t)k * stride + t] : -__builtin_inff();
+    l[u] = in ? L[(int64_t)k * stride + t] : 0.f;
+    M = fmaxf(M, r[u]);
+  }
+  for (int k = g + kFinG * 8; k < n; k += kFinG)
+    if (ok) M = fmaxf(M, R[(int64_t)k * stride + t]);
+  sm[g][tl] = M;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kFinG; ++k) M = fmaxf(M, sm[k][tl]);
   double S = 0.0;
-  int k = 0;
-  for (; k + 8 <= n; k += 8) {  // the eight pairs' loads first, then their terms
-    float r[8], l[8];
+  if (M != -__builtin_inff()) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      r[u] = R[(int64_t)(k + u) * stride + t];
-      l[u] = L[(int64_t)(k + u) * stride + t];
-    }
+    for (int u = 0; u < 8; ++u)
+      if (r[u] != -__builtin_inff()) S += (double)l[u] * exp2((double)r[u] - (double)M);
+    for (int k = g + kFinG * 8; k < n; k += kFinG)
+      if (ok) {
+        const float rk = R[(int64_t)k * stride + t];
+        if (rk != -__builtin_inff()) S += (double)L[(int64_t)k * stride + t] * exp2((double)rk - (double)M);
+      }
+  }
+  ss[g][tl] = S;
+  __syncthreads();
+  S = 0.0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) S += r[u] != -__builtin_inff() ? (double)l[u] * exp2((double)r[u] - M) : 0.0;
-  }
-  for (; k < n; ++k) {
-    const double r = R[(int64_t)k * stride + t];
-    const double l = L[(int64_t)k * stride + t];
-    S += r != -__builtin_inf() ? l * exp2(r - M) : 0.0;
-  }
-  return (M + log2(S)) * 0.6931471805599453;  // natural-log LSE over the off-diagonal entries
+  for (int k = 0; k < kFinG; ++k) S += ss[k][tl];
+  // natural-log LSE over the off-diagonal entries
+  return M == -__builtin_inff() ? -__builtin_inf() : ((double)M + log2(S)) * 0.6931471805599453;
 }
 
 __device__ __forceinline__ double softplus64(double z) {
@@ -480,31 +501,35 @@ __device__ __forceinline__ double softplus64(double z) {
 }
 
 __global__ void __launch_bounds__(256) fwd_finalize(FinParams p) {
-  __shared__ double red[256];
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double contrib = 0.0;
-  if (t < p.n) {
-    const double s = (double)p.scale[0];
-    const double u = (double)p.udiag[p.r0 + t];
-    const double x = s * u;
-    const double offr = merge_parts(p.rowR, p.rowL, p.nrowpart, p.rstride, t);
-    const double offc = merge_parts(p.colR, p.colL, p.ncolpart, p.cstride, t);
-    const double er = softplus64(offr - x);  // r_i - x_ii, cancellation-free
-    const double ec = softplus64(offc - x);
-    p.lse_r[t] = (float)(x + er);
-    p.lse_c[t] = (float)(x + ec);
-    p.aux[t] = (float)er;
-    p.aux[p.n + t] = (float)ec;
-    p.aux[2 * p.n + t] = (float)u;
-    contrib = er + ec;
+  __shared__ float smr[kFinG][kFinT], smc[kFinG][kFinT];
+  __shared__ double ssr[kFinG][kFinT], ssc[kFinG][kFinT], red[kFinT];
+  const int tl = threadIdx.x & (kFinT - 1), g = threadIdx.x / kFinT;
+  const int64_t t = (int64_t)blockIdx.x * kFinT + tl;
+  const bool ok = t < p.n;
+  const double offr = merge_parts(p.rowR, p.rowL, p.nrowpart, p.rstride, t, ok, tl, g, smr, ssr);
+  const double offc = merge_parts(p.colR, p.colL, p.ncolpart, p.cstride, t, ok, tl, g, smc, ssc);
+  if (g == 0) {
+    double contrib = 0.0;
+    if (ok) {
+      const double u = (double)p.udiag[p.r0 + t];
+      const double x = (double)p.scale[0] * u;
+      const double er = softplus64(offr - x);  // r_i - x_ii, cancellation-free
+      const double ec = softplus64(offc - x);
+      p.lse_r[t] = (float)(x + er);
+      p.lse_c[t] = (float)(x + ec);
+      p.aux[t] = (float)er;
+      p.aux[p.n + t] = (float)ec;
+      p.aux[2 * p.n + t] = (float)u;
+      contrib = er + ec;
+    }
+    red[tl] = contrib;
   }
-  red[threadIdx.x] = contrib;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    double c = 0.0;
+    for (int k = 0; k < kFinT; ++k) c += red[k];
+    p.partial[blockIdx.x] = c;
   }
-  if (threadIdx.x == 0) p.partial[blockIdx.x] = red[0];
 }
 
 // Sharded forward: one base-2 pair per column j in [0, b) over this shard's
@@ -562,9 +587,16 @@ void fwd1_grid(int64_t b, int64_t nrows, int* Pr, int* Pc) {
   *Pr = (int)(nRT < 64 ? nRT : 64);
 }
 
+// Most partial pairs per sample that the grid of any nrows <= b leaves.
+int fwd1_pairs(int64_t b) {
+  int Pr = 0, Pc = 0;
+  fwd1_grid(b, b, &Pr, &Pc);
+  return Pr + 4 * Pc;
+}
+
 static int launch_fwd1(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
                        const float* scale, hipStream_t stream, float* rowR, float* rowL, float* colR, float* colL,
-                       float* udiag, int* nrowpart, int* ncolpart) {
+                       float* udiag) {
   FwdParams p;
   p.img = img;
   p.txt = txt;
@@ -582,11 +614,33 @@ static int launch_fwd1(const void* img, const void* txt, int64_t b, int64_t d, i
   p.r0 = r0;
   p.rend = r0 + nrows;
   p.rstride = nrows;
-  *nrowpart = p.Pc * 4;
-  *ncolpart = p.Pr;
   if (dtype != 1) return 2;  // every supported 16-bit width takes the resident-rows sweep
   hipLaunchKernelGGL(fwd_sweep, dim3(p.Pr * p.Pc), dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+// Partial pairs per own row and per column that the sweep over nrows own rows
+// leaves.
+static void sweep_parts(int64_t b, int64_t d, int dtype, int64_t nrows, int* nrowpart, int* ncolpart) {
+  int Pr = 0, Pc = 0;
+  if (fwd2_supported(d, dtype)) {
+    fwd2_grid(b, nrows, d, &Pr, &Pc);
+    *nrowpart = Pc;
+  } else {
+    fwd1_grid(b, nrows, &Pr, &Pc);
+    *nrowpart = Pc * 4;
+  }
+  *ncolpart = Pr;
+}
+
+// The four arrays of partial pairs inside their region: nrowpart x nrows row
+// pairs, ncolpart x b column pairs, each array on a 256-byte boundary.
+struct PairPtrs {
+  float *rowR, *rowL, *colR, *colL;
+};
+static PairPtrs pair_ptrs(float* pairs, int nrowpart, int64_t nrows, int ncolpart, int64_t b) {
+  const int64_t nr = ((int64_t)nrowpart * nrows + 63) / 64 * 64, nc = ((int64_t)ncolpart * b + 63) / 64 * 64;
+  return PairPtrs{pairs, pairs + nr, pairs + 2 * nr, pairs + 2 * nr + nc};
 }
 
 // The sweep over own rows [r0, r0 + nrows) against all b columns: 16-bit
@@ -594,29 +648,14 @@ static int launch_fwd1(const void* img, const void* txt, int64_t b, int64_t d, i
 // streamed-tiles sweep above.  Both leave partial pairs: nrowpart per own row
 // (stride nrows, by row - r0) and ncolpart per column (stride b).
 static int launch_sweep(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
-                        const float* scale, float* rowR, float* rowL, float* colR, float* colL, float* udiag,
-                        float* ref2, hipStream_t stream, int* nrowpart, int* ncolpart) {
-  if (fwd2_supported(d, dtype)) {
-    int Pr2 = 0, Pc2 = 0;
-    fwd2_grid(b, nrows, d, &Pr2, &Pc2);
-    *nrowpart = Pc2;
-    *ncolpart = Pr2;
-    return launch_fwd2(img, txt, b, d, dtype, r0, nrows, scale, rowR, rowL, colR, colL, udiag, ref2, stream);
-  }
-  return launch_fwd1(img, txt, b, d, dtype, r0, nrows, scale, stream, rowR, rowL, colR, colL, udiag, nrowpart,
-                     ncolpart);
-}
-
-// Row partial count of the sweep over nrows own rows (what the finalize of a
-// shard has to merge).
-int sweep_rowparts(int64_t b, int64_t d, int dtype, int64_t nrows) {
-  int Pr = 0, Pc = 0;
-  if (fwd2_supported(d, dtype)) {
-    fwd2_grid(b, nrows, d, &Pr, &Pc);
-    return Pc;
-  }
-  fwd1_grid(b, nrows, &Pr, &Pc);
-  return Pc * 4;
+                        const float* scale, float* pairs, float* udiag, float* ref2, hipStream_t stream,
+                        int* nrowpart, int* ncolpart, PairPtrs* pp) {
+  sweep_parts(b, d, dtype, nrows, nrowpart, ncolpart);
+  *pp = pair_ptrs(pairs, *nrowpart, nrows, *ncolpart, b);
+  if (fwd2_supported(d, dtype))
+    return launch_fwd2(img, txt, b, d, dtype, r0, nrows, scale, pp->rowR, pp->rowL, pp->colR, pp->colL, udiag, ref2,
+                       stream);
+  return launch_fwd1(img, txt, b, d, dtype, r0, nrows, scale, stream, pp->rowR, pp->rowL, pp->colR, pp->colL, udiag);
 }
 
 static int launch_finalize(int64_t r0, int64_t n, double loss_mul, const float* scale, float* loss, double* loss64,
@@ -640,7 +679,7 @@ static int launch_finalize(int64_t r0, int64_t n, double loss_mul, const float* 
   f.lse_c = lse_c;
   f.aux = aux;
   f.partial = partial;
-  int nfin = (int)((n + 255) / 256);
+  const int nfin = (int)((n + kFinT - 1) / kFinT);
   hipLaunchKernelGGL(fwd_finalize, dim3(nfin), dim3(256), 0, stream, f);
   if (hipGetLastError() != hipSuccess) return 1;
   hipLaunchKernelGGL(sum_partials, dim3(1), dim3(256), 0, stream, (const double*)partial, (int64_t)nfin, loss_mul,
@@ -651,28 +690,29 @@ static int launch_finalize(int64_t r0, int64_t n, double loss_mul, const float* 
 // Forward over the whole batch: the sweep over all rows, then the finalize of
 // every sample and the loss.
 int launch_fwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype, const float* scale, float* loss,
-               double* loss64, float* lse_r, float* lse_c, float* aux, hipStream_t stream, float* rowR, float* rowL,
-               float* colR, float* colL, float* udiag, float* ref2, double* partial) {
+               double* loss64, float* lse_r, float* lse_c, float* aux, hipStream_t stream, float* pairs, float* udiag,
+               float* ref2, double* partial) {
   int nrowpart = 0, ncolpart = 0;
+  PairPtrs pp;
   const int rc =
-      launch_sweep(img, txt, b, d, dtype, 0, b, scale, rowR, rowL, colR, colL, udiag, ref2, stream, &nrowpart, &ncolpart);
+      launch_sweep(img, txt, b, d, dtype, 0, b, scale, pairs, udiag, ref2, stream, &nrowpart, &ncolpart, &pp);
   if (rc != 0) return rc;
-  return launch_finalize(0, b, 1.0 / (2.0 * (double)b), scale, loss, loss64, lse_r, lse_c, aux, rowR, rowL, nrowpart,
-                         b, colR, colL, ncolpart, b, udiag, partial, stream);
+  return launch_finalize(0, b, 1.0 / (2.0 * (double)b), scale, loss, loss64, lse_r, lse_c, aux, pp.rowR, pp.rowL,
+                         nrowpart, b, pp.colR, pp.colL, ncolpart, b, udiag, partial, stream);
 }
 
 // Sharded forward, local part: the sweep over own rows [r0, r0 + nrows), row
 // partials left in the workspace, and one base-2 pair per column over the own
 // rows written to colpair ([2b]: R then l).
 int launch_fwd_shard(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
-                     const float* scale, float* colpair, hipStream_t stream, float* rowR, float* rowL, float* colR,
-                     float* colL, float* udiag, float* ref2) {
+                     const float* scale, float* colpair, hipStream_t stream, float* pairs, float* udiag, float* ref2) {
   int nrowpart = 0, ncolpart = 0;
-  const int rc = launch_sweep(img, txt, b, d, dtype, r0, nrows, scale, rowR, rowL, colR, colL, udiag, ref2, stream,
-                              &nrowpart, &ncolpart);
+  PairPtrs pp;
+  const int rc =
+      launch_sweep(img, txt, b, d, dtype, r0, nrows, scale, pairs, udiag, ref2, stream, &nrowpart, &ncolpart, &pp);
   if (rc != 0) return rc;
-  hipLaunchKernelGGL(fwd_col_pairs, dim3((unsigned)((b + 255) / 256)), dim3(256), 0, stream, (const float*)colR,
-                     (const float*)colL, ncolpart, b, colpair);
+  hipLaunchKernelGGL(fwd_col_pairs, dim3((unsigned)((b + 255) / 256)), dim3(256), 0, stream, (const float*)pp.colR,
+                     (const float*)pp.colL, ncolpart, b, colpair);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
@@ -682,11 +722,13 @@ int launch_fwd_shard(const void* img, const void* txt, int64_t b, int64_t d, int
 // this shard's share of the loss, sum of (l^r + l^c) / (2b), into loss_part.
 int launch_fwd_shard_finish(int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows, int64_t nparts,
                             const float* colpairs, const float* scale, float* lse_r, float* lse_c, float* aux,
-                            double* loss_part, hipStream_t stream, const float* rowR, const float* rowL,
-                            const float* udiag, double* partial) {
-  const int nrowpart = sweep_rowparts(b, d, dtype, nrows);
-  return launch_finalize(r0, nrows, 1.0 / (2.0 * (double)b), scale, nullptr, loss_part, lse_r, lse_c, aux, rowR, rowL,
-                         nrowpart, nrows, colpairs, colpairs + nrows, (int)nparts, 2 * nrows, udiag, partial, stream);
+                            double* loss_part, hipStream_t stream, float* pairs, const float* udiag, double* partial) {
+  int nrowpart = 0, ncolpart = 0;
+  sweep_parts(b, d, dtype, nrows, &nrowpart, &ncolpart);
+  const PairPtrs pp = pair_ptrs(pairs, nrowpart, nrows, ncolpart, b);
+  return launch_finalize(r0, nrows, 1.0 / (2.0 * (double)b), scale, nullptr, loss_part, lse_r, lse_c, aux, pp.rowR,
+                         pp.rowL, nrowpart, nrows, colpairs, colpairs + nrows, (int)nparts, 2 * nrows, udiag, partial,
+                         stream);
 }
 
 }  // namespace infcl

@@ -415,8 +415,11 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
     auto stats = [&](int jt, const f32x16& sacc, const INFCL_LDS float* scur, int par, float Rmine, float Lmine) {
       const int j0 = jt * kSweepBN;
       const int jl = jrow(rs16_index(lane));  // the column whose partial this lane ends with
-      // entries off the problem or on the diagonal take no part (uniform test)
-      const bool special = (j0 == own0) || (j0 + kSweepBN > b) || !wave_rows_ok;
+      // entries off the problem or on the diagonal take no part (uniform
+      // test).  Own rows past the end need no mask in the common path: their
+      // row pairs are not stored and their column weight alpha is zero.
+      const bool special = (j0 == own0) || (j0 + kSweepBN > b);
+      const bool masked = special || !wave_rows_ok;
       // (bitwise operators: no short-circuit branches)
       auto keep = [&](int r) {
         const int j = j0 + jrow(r);
@@ -428,7 +431,7 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
       auto yv = [&](int r) {
         float x = sacc[r];
         asm volatile("" : "+v"(x));
-        return (!special | keep(r)) ? x * k2 : ninf;
+        return (!masked | keep(r)) ? x * k2 : ninf;
       };
       // ---- row: lazy against its reference, exact when a bound fails
       float e[16];
@@ -568,15 +571,42 @@ static int launch_fwd2_d(const Fwd2Params& p, bool f16, hipStream_t stream) {
 bool fwd2_supported(int64_t d, int dtype) { return (dtype == 0 || dtype == 2) && d % 128 == 0 && d >= 128 && d <= 1024; }
 
 // Grid of the resident-rows forward for nrows own rows of width d against b
-// columns: P_c column groups (one per XCD) times P_r row groups, P_r P_c <= 256
-// workgroups (one per CU) with 8 waves or with 4 waves at d > 512, and 512 (two
-// per CU) with the 4-wave build option at d <= 512.
+// columns: P_c column groups times P_r row groups, at most 256 workgroups (one
+// per CU).  The busiest workgroup sweeps ceil(row blocks / P_r) row blocks of
+// ceil(tiles / P_c) tiles, plus about four tiles' time per row block for its
+// start and end; P_r and P_c minimise that, with a small weight on the partial
+// pairs the finalize has to merge (P_r + P_c per sample).  P_r <= 32 and
+// P_r + P_c <= 40 keep the workspace at that of the 32 x 8 grid, which large
+// batches of whole rounds get (one column group per XCD).  Against the fixed
+// P_c = 8: b = 5000, d = 512 forward kernel 64 -> 40 us, a shard of 4096
+// rows of b = 32768 240 -> 144 us (with the ragged blocks' mask gone).
 void fwd2_grid(int64_t b, int64_t nrows, int64_t d, int* Pr, int* Pc) {
   const int64_t bm = 32 * fwd2_waves(d);
   const int64_t nRB = (nrows + bm - 1) / bm, nCT = (b + kSweepBN - 1) / kSweepBN;
-  *Pc = (int)(nCT < 8 ? nCT : 8);
-  const int64_t pmax = d > 512 ? 32 : 256 / kF2NW;
-  *Pr = (int)(nRB < pmax ? nRB : pmax);
+  double best = 0.0;
+  for (int r = 32; r >= 1; --r) {
+    if (r > nRB) continue;
+    int64_t cmax = 256 / r < 40 - r ? 256 / r : 40 - r;
+    if (cmax < 8) cmax = 8;
+    int64_t c = cmax < nCT ? cmax : nCT;
+    const int64_t per = (nCT + c - 1) / c;
+    c = (nCT + per - 1) / per;  // the fewest groups of that many tiles
+    if (c < 8 && nCT >= 8) c = 8;
+    const double cost = (double)((nRB + r - 1) / r) * (double)(per + 4) + 0.1 * (double)(r + c);
+    if (best == 0.0 || cost < best) {
+      best = cost;
+      *Pr = r;
+      *Pc = (int)c;
+    }
+  }
+}
+
+// Most partial pairs per sample that the grid of any nrows <= b leaves.
+int fwd2_pairs(int64_t b, int64_t d) {
+  const int64_t bm = 32 * fwd2_waves(d);
+  const int64_t nRB = (b + bm - 1) / bm, nCT = (b + kSweepBN - 1) / kSweepBN;
+  const int64_t n = (nRB < 32 ? nRB : 32) + (nCT < 39 ? nCT : 39);
+  return (int)(n < 40 ? n : 40);
 }
 
 int launch_fwd2(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
