@@ -33,7 +33,8 @@ constexpr int kSingleBM = 64;  // own image rows per workgroup
 
 __global__ void dscale_finish(const double* part, int64_t n, int64_t b, const float* dloss, float* dscale,
                               double* dscale64);
-__global__ void lse_to_log2(const float* lse_r, const float* lse_c, float* l2r, float* l2c, int64_t b);
+__global__ void bwd_prep(const float* lse_r, const float* lse_c, const float* aux, float* l2r, float* l2c, float* g16,
+                         int64_t b);
 
 struct SingleParams {
   const __bf16* img;   // own rows i, [b, d]
@@ -369,8 +370,7 @@ extern "C" int infcl_ablation_bwd_single(const void* img, const void* txt, int64
   float* l2c = l2r + b;
   double* ds_part = (double*)((char*)workspace + lse2_bytes);
   hipStream_t st = (hipStream_t)stream;
-  const unsigned nblk = (unsigned)((b + 255) / 256);
-  hipLaunchKernelGGL(lse_to_log2, dim3(nblk), dim3(256), 0, st, lse_r, lse_c, l2r, l2c, b);
+  hipLaunchKernelGGL(bwd_prep, dim3(kPrepBlocks), dim3(256), 0, st, lse_r, lse_c, aux, l2r, l2c, (float*)nullptr, b);
   hipLaunchKernelGGL(zero_f32, dim3(2048), dim3(256), 0, st, dtxt, b * d);
   SingleParams p;
   p.img = (const __bf16*)img;

@@ -89,7 +89,7 @@ Layout make_layout(int64_t b, int64_t d, int dtype) {
   L.fwd_total = off;
   L.lse2 = off; off = align256(off + 2 * fb);
   L.bwd_part = off; off = align256(off + (size_t)2 * ((b + 63) / 64) * sizeof(double));  // 64 or 128 rows per WG
-  L.g16 = off; off = align256(off + (dtype == INFCL_F16 ? (size_t)(2 + 2 * ((b + 255) / 256)) * sizeof(float) : 0));
+  L.g16 = off; off = align256(off + (dtype == INFCL_F16 ? (size_t)(2 * infcl::kPrepBlocks) * sizeof(float) : 0));
   L.gpad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * sizeof(float) : 0));  // dimg, dtxt
   // partial sums: in place of the pairs, or, where those are too few, at the end
   L.part = L.pairs;
@@ -132,10 +132,13 @@ size_t noalloc_need(int64_t b, int64_t d, int dtype) {
   return n;
 }
 
-// Row copy between widths: rows of cin 16-byte chunks into rows of cout
-// chunks, cut or zero-filled at the end.
-__global__ void __launch_bounds__(256) copy_rows(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t rows,
+// Row copies between widths, both sides' in one launch: rows of cin 16-byte
+// chunks into rows of cout chunks, cut or zero-filled at the end.
+__global__ void __launch_bounds__(256) copy_rows(const uint4* __restrict__ src0, const uint4* __restrict__ src1,
+                                                 uint4* __restrict__ dst0, uint4* __restrict__ dst1, int64_t rows,
                                                  int cin, int cout) {
+  const uint4* __restrict__ src = blockIdx.y ? src1 : src0;
+  uint4* __restrict__ dst = blockIdx.y ? dst1 : dst0;
   const int64_t n = rows * cout;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t r = i / cout;
@@ -144,7 +147,7 @@ __global__ void __launch_bounds__(256) copy_rows(const uint4* __restrict__ src, 
   }
 }
 
-unsigned copy_grid(int64_t n) { return (unsigned)(n / 256 + 1 < 65536 ? n / 256 + 1 : 65536); }
+dim3 copy_grid(int64_t n) { return dim3((unsigned)(n / 256 + 1 < 65536 ? n / 256 + 1 : 65536), 2); }
 
 // The inputs the sweeps read: img and txt as given, or, when d is not a width
 // the sweeps are built for, their zero-padded copies in the workspace.
@@ -156,8 +159,8 @@ bool stage_inputs(const void*& img, const void*& txt, int64_t b, int64_t d, int 
   const int64_t n = b * cout;
   uint4* pi = (uint4*)(ws + L.pad);
   uint4* pt = pi + n;
-  hipLaunchKernelGGL(copy_rows, dim3(copy_grid(n)), dim3(256), 0, stream, (const uint4*)img, pi, b, cin, cout);
-  hipLaunchKernelGGL(copy_rows, dim3(copy_grid(n)), dim3(256), 0, stream, (const uint4*)txt, pt, b, cin, cout);
+  hipLaunchKernelGGL(copy_rows, copy_grid(n), dim3(256), 0, stream, (const uint4*)img, (const uint4*)txt, pi, pt, b, cin,
+                     cout);
   if (hipGetLastError() != hipSuccess) return false;
   img = pi;
   txt = pt;
@@ -188,8 +191,8 @@ bool unstage_grads(void* dimg, void* dtxt, int64_t rows, int64_t b, int64_t d, s
   const uint4* gi = (const uint4*)(ws + L.gpad);
   const uint4* gt = gi + b * cin;
   const int64_t n = rows * cout;
-  hipLaunchKernelGGL(copy_rows, dim3(copy_grid(n)), dim3(256), 0, stream, gi, (uint4*)dimg, rows, cin, cout);
-  hipLaunchKernelGGL(copy_rows, dim3(copy_grid(n)), dim3(256), 0, stream, gt, (uint4*)dtxt, rows, cin, cout);
+  hipLaunchKernelGGL(copy_rows, copy_grid(n), dim3(256), 0, stream, gi, gt, (uint4*)dimg, (uint4*)dtxt, rows, cin,
+                     cout);
   return hipGetLastError() == hipSuccess;
 }
 

@@ -107,9 +107,10 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   const float s = p.scale[0];
   const float k2 = s * kLog2e;
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  // fp16: G' is rounded after scaling by alpha = g16[0], divided out at the end
-  const float g16a = F16 ? p.g16[0] : 1.0f;
-  const float kfin = dl * s / (2.0f * (float)b) * (F16 ? p.g16[1] : 1.0f);
+  // fp16: G' is rounded after scaling by alpha = 2^g16e, divided out at the end
+  const int g16e = F16 ? g16_exponent(p.g16) : 0;
+  const float g16a = F16 ? ldexpf(1.f, g16e) : 1.0f;
+  const float kfin = dl * s / (2.0f * (float)b) * (F16 ? ldexpf(1.f, -g16e) : 1.0f);
 
   // own operand of GEMM1, held for the whole sweep: row irow, slots 8h..8h+7 of each step
   typedef typename std::conditional<ES == 2, bf16x8, f32x4>::type frag_t;
@@ -543,45 +544,10 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   if (threadIdx.x == 0) p.ds_part[blockIdx.x] = red[0];
 }
 
-// Gradients of the split row blocks: the ns partial sums of each element in
-// fixed order, scaled as the sweeps scale theirs and rounded once to the
-// gradient type.  Bound by memory (the partials are read once, 16 bytes per
-// lane); at most kPartBytes of them, which stay in the last-level cache.
-template <bool G16, bool F16>
-__global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm) {
-  using GO = GradOut<G16, F16>;
-  const int c4 = (int)(p.d >> 2);  // 4-feature groups per row
-  const int per = bm * c4;         // ... per block
-  const int q = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int blk = p.nfull + q;
-  const int sd = blk >= p.nblk ? 1 : 0;
-  const int rl = e / c4;
-  const int64_t row = (int64_t)(sd ? blk - p.nblk : blk) * bm + rl;  // own row - own_off
-  if (e >= per || row >= p.own_end - p.own_off) return;
-  const float s = p.scale[0];
-  const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  const float kfin = dl * s / (2.0f * (float)p.b) * (F16 ? p.g16[1] : 1.0f);
-  const f32x4* src = (const f32x4*)(p.part + (int64_t)q * p.ns * per * 4) + e;
-  f32x4 a = {0.f, 0.f, 0.f, 0.f};
-  int k = 0;
-  for (; k + 4 <= p.ns; k += 4) {  // four loads in flight, added in order
-    f32x4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = src[(int64_t)(k + u) * per];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) a += v[u];
-  }
-  for (; k < p.ns; ++k) a += src[(int64_t)k * per];
-  auto* dst = (typename GO::type*)p.side[sd].dOwn + row * p.d + 4 * (e - rl * c4);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) dst[u] = GO::cvt(kfin * a[u]);
-}
-
-// dscale = dloss / (2b) * (sum of both launches' partials), fixed order; into
-// dscale (fp32) and/or dscale64 (fp64), whichever is given
-__global__ void __launch_bounds__(256) dscale_finish(const double* part, int64_t n, int64_t b, const float* dloss,
-                                                     float* dscale, double* dscale64) {
+// dscale = dloss / (2b) * (sum of the sweeps' partials), fixed order, by one
+// workgroup of 256; into dscale (fp32) and/or dscale64 (fp64), whichever is given
+__device__ __forceinline__ void dscale_sum(const double* part, int64_t n, int64_t b, const float* dloss, float* dscale,
+                                           double* dscale64) {
   __shared__ double red[256];
   double s = 0.0;
   for (int64_t k = threadIdx.x; k < n; k += 256) s += part[k];
@@ -597,6 +563,53 @@ __global__ void __launch_bounds__(256) dscale_finish(const double* part, int64_t
     if (dscale) *dscale = (float)v;
     if (dscale64) *dscale64 = v;
   }
+}
+__global__ void __launch_bounds__(256) dscale_finish(const double* part, int64_t n, int64_t b, const float* dloss,
+                                                     float* dscale, double* dscale64) {
+  dscale_sum(part, n, b, dloss, dscale, dscale64);
+}
+
+// Gradients of the split row blocks: the ns partial sums of each element in
+// fixed order, scaled as the sweeps scale theirs and rounded once to the
+// gradient type.  Bound by memory (the partials are read once, 16 bytes per
+// lane; at most 64 MiB of them, which stay in the last-level cache: 12 us).
+// One more workgroup (the last grid row) sums dscale: as a launch of its own
+// that took 4.7 us.
+template <bool G16, bool F16>
+__global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, float* dscale, double* dscale64) {
+  using GO = GradOut<G16, F16>;
+  if (blockIdx.y == gridDim.y - 1) {
+    if (blockIdx.x == 0) dscale_sum(p.ds_part, nwg, p.b, p.dloss, dscale, dscale64);
+    return;
+  }
+  const int c4 = (int)(p.d >> 2);  // 4-feature groups per row
+  const int per = bm * c4;         // ... per block
+  const int q = blockIdx.y;
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int blk = p.nfull + q;
+  const int sd = blk >= p.nblk ? 1 : 0;
+  const int rl = e / c4;
+  const int64_t row = (int64_t)(sd ? blk - p.nblk : blk) * bm + rl;  // own row - own_off
+  const float s = p.scale[0];
+  const float dl = p.dloss ? p.dloss[0] : 1.0f;
+  const float kfin = dl * s / (2.0f * (float)p.b) * (F16 ? ldexpf(1.f, -g16_exponent(p.g16)) : 1.0f);
+  if (e >= per || row >= p.own_end - p.own_off) return;
+  const f32x4* src = (const f32x4*)(p.part + (int64_t)q * p.ns * per * 4) + e;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  int k = 0;
+  for (; k + 4 <= p.ns; k += 4) {  // four loads in flight, added in order
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = src[(int64_t)(k + u) * per];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a += v[u];
+  }
+  for (; k < p.ns; ++k) a += src[(int64_t)k * per];
+  typedef typename GO::type out4 __attribute__((ext_vector_type(4)));
+  out4 o;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) o[u] = GO::cvt(kfin * a[u]);
+  *(out4*)((typename GO::type*)p.side[sd].dOwn + row * p.d + 4 * (e - rl * c4)) = o;
 }
 
 // Pass width: largest FB (32-feature blocks) dividing d/32 whose accumulators
@@ -656,73 +669,37 @@ static int launch_bwd_t(const BwdParams& p, int nwg, hipStream_t stream) {
   return 2;
 }
 
-// fp16 inputs: G' is rounded to fp16 after multiplication by a power of two
-// alpha, and the fp32 accumulators are multiplied by 1/alpha at the end (exact
-// scaling, the role loss scaling plays in mixed-precision training): without
-// it the G' of a well-separated batch (loss near zero) lies below fp16's
-// smallest subnormal, 2^-24, and the gradients would vanish.  alpha maps a
-// bound B on every |G'| to at most 2^14 (fp16's largest finite value is about
-// 2^16): off the diagonal P^r_ij <= 1 - P^r_ii = -expm1(-l^r_i) and
-// P^c_ij <= -expm1(-l^c_j), and |G'_ii| <= -expm1(-l^r_i) - expm1(-l^c_i), so
-// B = max_i(-expm1(-l^r_i)) + max_j(-expm1(-l^c_j)).
-// Per-block maxima (fixed-order tree) of the two terms, then alpha.
-__global__ void __launch_bounds__(256) g16_bound_part(const float* aux, int64_t b, float* part) {
-  __shared__ float sr[256], sc[256];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  sr[threadIdx.x] = i < b ? -expm1f(-aux[i]) : 0.f;
-  sc[threadIdx.x] = i < b ? -expm1f(-aux[b + i]) : 0.f;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sr[threadIdx.x] = fmaxf(sr[threadIdx.x], sr[threadIdx.x + w]);
-      sc[threadIdx.x] = fmaxf(sc[threadIdx.x], sc[threadIdx.x + w]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = sr[0];
-    part[2 * blockIdx.x + 1] = sc[0];
-  }
-}
-__global__ void __launch_bounds__(256) g16_scale_finish(const float* part, int64_t nblk, float* g16) {
-  __shared__ float sr[256], sc[256];
+// Before the sweeps: the log-sum-exp vectors rescaled to base 2 (the swept
+// side is streamed through LDS next to every tile and used as is), and for
+// fp16 (g16 given) the maxima behind the scale of G' (see g16_exponent).
+// kPrepBlocks workgroups for any b, so that the maxima are one pair per lane.
+__global__ void __launch_bounds__(256) bwd_prep(const float* lse_r, const float* lse_c, const float* aux, float* l2r,
+                                                float* l2c, float* g16, int64_t b) {
   float mr = 0.f, mc = 0.f;
-  for (int64_t k = threadIdx.x; k < nblk; k += 256) {
-    mr = fmaxf(mr, part[2 * k]);
-    mc = fmaxf(mc, part[2 * k + 1]);
-  }
-  sr[threadIdx.x] = mr;
-  sc[threadIdx.x] = mc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sr[threadIdx.x] = fmaxf(sr[threadIdx.x], sr[threadIdx.x + w]);
-      sc[threadIdx.x] = fmaxf(sc[threadIdx.x], sc[threadIdx.x + w]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const float B = sr[0] + sc[0];
-    int k = 0;
-    if (B > 0.f) {
-      int e;
-      (void)frexpf(B, &e);  // B = m 2^e, m in [0.5, 1): alpha B = m 2^14 < 2^14
-      k = 14 - e;
-      k = k > 100 ? 100 : k;
-    }
-    g16[0] = ldexpf(1.f, k);
-    g16[1] = ldexpf(1.f, -k);
-  }
-}
-
-// Log-sum-exp vectors rescaled to base 2 (the swept side is streamed through
-// LDS next to every tile and used as is).
-__global__ void __launch_bounds__(256) lse_to_log2(const float* lse_r, const float* lse_c, float* l2r, float* l2c,
-                                                   int64_t b) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < b) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < b; i += (int64_t)kPrepBlocks * 256) {
     l2r[i] = lse_r[i] * kLog2e;
     l2c[i] = lse_c[i] * kLog2e;
+    if (g16) {
+      mr = fmaxf(mr, -expm1f(-aux[i]));
+      mc = fmaxf(mc, -expm1f(-aux[b + i]));
+    }
+  }
+  if (g16) {
+    __shared__ float sr[4], sc[4];
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+      mr = fmaxf(mr, shfl_xor(mr, k));
+      mc = fmaxf(mc, shfl_xor(mc, k));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      sr[threadIdx.x >> 6] = mr;
+      sc[threadIdx.x >> 6] = mc;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      g16[2 * blockIdx.x] = fmaxf(fmaxf(sr[0], sr[1]), fmaxf(sr[2], sr[3]));
+      g16[2 * blockIdx.x + 1] = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+    }
   }
 }
 
@@ -792,14 +769,9 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
   const BwdPlan pl = plan_bwd(b, nrows, d, dtype, part_cap);
   float* l2r = lse2;
   float* l2c = lse2 + b;
-  const unsigned nblk = (unsigned)((b + 255) / 256);
-  hipLaunchKernelGGL(lse_to_log2, dim3(nblk), dim3(256), 0, stream, lse_r, lse_c, l2r, l2c, b);
+  hipLaunchKernelGGL(bwd_prep, dim3(kPrepBlocks), dim3(256), 0, stream, lse_r, lse_c, aux, l2r, l2c,
+                     dtype == 2 ? g16 : nullptr, b);
   if (hipGetLastError() != hipSuccess) return 1;
-  if (dtype == 2) {  // g16 = (alpha, 1/alpha) followed by 2 nblk block maxima
-    hipLaunchKernelGGL(g16_bound_part, dim3(nblk), dim3(256), 0, stream, aux, b, g16 + 2);
-    hipLaunchKernelGGL(g16_scale_finish, dim3(1), dim3(256), 0, stream, (const float*)(g16 + 2), (int64_t)nblk, g16);
-    if (hipGetLastError() != hipSuccess) return 1;
-  }
   BwdParams p;
   p.g16 = g16;
   p.b = b;
@@ -829,16 +801,20 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
     rc = launch_bwd_t<float>(p, pl.nwg, stream);
   if (rc) return rc;
   if (pl.ns > 1) {
-    const dim3 grid((unsigned)((pl.bm * (d >> 2) + 255) / 256), (unsigned)split);
+    const dim3 grid((unsigned)((pl.bm * (d >> 2) + 255) / 256), (unsigned)split + 1);
     if (dtype == 2 && gdt)
-      hipLaunchKernelGGL((bwd_reduce<true, true>), grid, dim3(256), 0, stream, p, pl.bm);
+      hipLaunchKernelGGL((bwd_reduce<true, true>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,
+                         dscale64);
     else if (dtype == 2)
-      hipLaunchKernelGGL((bwd_reduce<false, true>), grid, dim3(256), 0, stream, p, pl.bm);
+      hipLaunchKernelGGL((bwd_reduce<false, true>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,
+                         dscale64);
     else if (gdt)
-      hipLaunchKernelGGL((bwd_reduce<true, false>), grid, dim3(256), 0, stream, p, pl.bm);
+      hipLaunchKernelGGL((bwd_reduce<true, false>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,
+                         dscale64);
     else
-      hipLaunchKernelGGL((bwd_reduce<false, false>), grid, dim3(256), 0, stream, p, pl.bm);
-    if (hipGetLastError() != hipSuccess) return 1;
+      hipLaunchKernelGGL((bwd_reduce<false, false>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,
+                         dscale64);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
   }
   hipLaunchKernelGGL(dscale_finish, dim3(1), dim3(256), 0, stream, (const double*)p.ds_part, (int64_t)pl.nwg, b,
                      dloss, dscale, dscale64);

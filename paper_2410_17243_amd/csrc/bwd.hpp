@@ -27,7 +27,7 @@ struct BwdParams {
   const float* dloss;  // device scalar or nullptr (= 1)
   int64_t own_off, own_end;  // own rows [own_off, own_end) of both sides (a shard; 0 and b for the whole batch)
   double* ds_part;           // [gridDim.x]
-  const float* g16;          // fp16 inputs: (alpha, 1/alpha), the power of two G' is scaled by
+  const float* g16;          // fp16 inputs: block maxima for the scale of G' (g16_scale)
   int gdt;                   // gradient type, which chooses the kernel instantiation: 0 fp32, 1 16-bit
   // Work split (plan_bwd): of the 2 nblk row blocks (image side first) the
   // first nfull are swept whole, one workgroup each; each of the others is
@@ -81,6 +81,37 @@ struct BwdPlan {
 };
 
 constexpr int kWideBM = 64;  // own rows per workgroup of the wide-row sweeps
+
+// fp16 inputs: G' is rounded to fp16 after multiplication by a power of two
+// alpha, and the fp32 accumulators are multiplied by 1/alpha at the end (exact
+// scaling, the role loss scaling plays in mixed-precision training): without
+// it the G' of a well-separated batch (loss near zero) lies below fp16's
+// smallest subnormal, 2^-24, and the gradients would vanish.  alpha maps a
+// bound B on every |G'| to at most 2^14 (fp16's largest finite value is about
+// 2^16): off the diagonal P^r_ij <= 1 - P^r_ii = -expm1(-l^r_i) and
+// P^c_ij <= -expm1(-l^c_j), and |G'_ii| <= -expm1(-l^r_i) - expm1(-l^c_i), so
+// B = max_i(-expm1(-l^r_i)) + max_j(-expm1(-l^c_j)).
+// bwd_prep leaves the two maxima of each of its kPrepBlocks blocks; every wave
+// that needs alpha reduces them itself (one pair per lane).
+constexpr int kPrepBlocks = 64;
+__device__ __forceinline__ int g16_exponent(const float* part) {
+  const int lane = __lane_id();
+  float mr = part[2 * lane], mc = part[2 * lane + 1];
+#pragma unroll
+  for (int k = 1; k < 64; k <<= 1) {
+    mr = fmaxf(mr, shfl_xor(mr, k));
+    mc = fmaxf(mc, shfl_xor(mc, k));
+  }
+  const float B = mr + mc;
+  int k = 0;
+  if (B > 0.f) {
+    int e;
+    (void)frexpf(B, &e);  // B = m 2^e, m in [0.5, 1): alpha B = m 2^14 < 2^14
+    k = 14 - e;
+    k = k > 100 ? 100 : k;
+  }
+  return __builtin_amdgcn_readfirstlane(k);
+}
 
 // Gradient element type of a sweep: fp32, or with G16 the 16-bit input type
 // (fp16 with F16, else bf16), rounded to nearest even from the fp32 gradient

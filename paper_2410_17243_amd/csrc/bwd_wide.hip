@@ -85,9 +85,10 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
   const float s = p.scale[0];
   const float k2 = s * kLog2e;
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  // fp16: G' is rounded after scaling by alpha = g16[0], divided out at the end
-  const float g16a = F16 ? p.g16[0] : 1.0f;
-  const float kfin = dl * s / (2.0f * (float)b) * (F16 ? p.g16[1] : 1.0f);
+  // fp16: G' is rounded after scaling by alpha = 2^g16e, divided out at the end
+  const int g16e = F16 ? g16_exponent(p.g16) : 0;
+  const float g16a = F16 ? ldexpf(1.f, g16e) : 1.0f;
+  const float kfin = dl * s / (2.0f * (float)b) * (F16 ? ldexpf(1.f, -g16e) : 1.0f);
 
   // own operand of GEMM1: row irow, features 16 (2 s2 + kh) + 8h .. +8
   bf16x8 ownf[KH];
@@ -416,8 +417,9 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   const float s = p.scale[0];
   const float k2 = s * kLog2e;
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  const float g16a = F16 ? p.g16[0] : 1.0f;
-  const float kfin = dl * s / (2.0f * (float)b) * (F16 ? p.g16[1] : 1.0f);
+  const int g16e = F16 ? g16_exponent(p.g16) : 0;
+  const float g16a = F16 ? ldexpf(1.f, g16e) : 1.0f;
+  const float kfin = dl * s / (2.0f * (float)b) * (F16 ? ldexpf(1.f, -g16e) : 1.0f);
 
   bf16x8 ownf[KH];
   {
