@@ -92,7 +92,7 @@ def _check(status: int, where: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # (the declared argument types convert an int)
 
 
 def _dtype_code(t) -> int:
@@ -110,7 +110,15 @@ def _dtype_code(t) -> int:
 def _stream(t):
     import torch
 
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _raw_stream(dev):
+    """Handle of the current stream of device dev (torch.cuda.current_stream
+    builds a Stream object for it: 2 us)."""
+    import torch
+
+    return torch._C._cuda_getCurrentRawStream(dev.index)
 
 
 # ------------------------------------------------------------------ C ABI names
@@ -270,23 +278,54 @@ def clip_loss_bwd(img, txt, scale, fwd: dict, dloss=None, workspace=None, grad_d
 def _make_function():
     import torch
 
+    # A small batch's step is bound by host time, so the function marshals its
+    # arguments itself: the per-sample outputs in one allocation (lse_r, lse_c
+    # and aux, each 16-byte aligned) and plain addresses (b = 256, d = 512:
+    # 185 -> 150 us per step).
     class ClipLoss(torch.autograd.Function):
         @staticmethod
         def forward(ctx, img, txt, scale):
-            f = clip_loss_fwd(img, txt, scale)
-            ctx.save_for_backward(img, txt, scale, f["lse_r"], f["lse_c"], f["aux"])
-            ctx.ws = f["workspace"]
-            return f["loss"]
+            _validate(img, txt, scale)
+            b, d = img.shape
+            dev = img.device
+            n = (b + 3) & ~3
+            stats = torch.empty(2 * n + 3 * b, dtype=torch.float32, device=dev)
+            loss = torch.empty((), dtype=torch.float32, device=dev)
+            ws = workspace_for(img)
+            p = stats.data_ptr()
+            _check(load_library().infcl_fwd(img.data_ptr(), txt.data_ptr(), b, d, _dtype_code(img), scale.data_ptr(),
+                                             loss.data_ptr(), None, p, p + 4 * n, p + 8 * n, ws.data_ptr(), ws.numel(),
+                                             _raw_stream(dev)), "infcl_fwd")
+            ctx.save_for_backward(img, txt, scale, stats)
+            ctx.ws = ws
+            return loss
 
         @staticmethod
         def backward(ctx, dloss):
-            img, txt, scale, lse_r, lse_c, aux = ctx.saved_tensors
-            fwd = {"lse_r": lse_r, "lse_c": lse_c, "aux": aux}
+            img, txt, scale, stats = ctx.saved_tensors  # (as saved-tensor hooks return them)
+            _validate(img, txt, scale)
+            b, d = img.shape
+            dev = img.device
+            n = (b + 3) & ~3
+            _check_vec(stats, 2 * n + 3 * b, "the saved statistics", dev)
+            ws = ctx.ws
+            _check_workspace(ws, dev)
+            if dloss.device != dev or dloss.numel() != 1:
+                raise ValueError(f"dloss must be one element on {dev}, got {tuple(dloss.shape)} on {dloss.device}")
+            if dloss.dtype != torch.float32:
+                dloss = dloss.to(torch.float32)
             # gradients in the inputs' dtype straight from the kernels (one
             # rounding of the fp32 accumulators, as a cast would do)
-            dimg, dtxt, dscale = clip_loss_bwd(img, txt, scale, fwd, dloss=dloss, workspace=ctx.ws,
-                                               grad_dtype=img.dtype)
-            return dimg, dtxt, dscale.reshape(scale.shape)
+            code = _dtype_code(img)
+            dimg = torch.empty((b, d), dtype=img.dtype, device=dev)
+            dtxt = torch.empty((b, d), dtype=img.dtype, device=dev)
+            dscale = torch.empty(scale.shape, dtype=torch.float32, device=dev)
+            p = stats.data_ptr()
+            _check(load_library().infcl_bwd(img.data_ptr(), txt.data_ptr(), b, d, code, scale.data_ptr(), p, p + 4 * n,
+                                             p + 8 * n, dloss.data_ptr(), dimg.data_ptr(), dtxt.data_ptr(), code,
+                                             dscale.data_ptr(), ws.data_ptr(), ws.numel(), _raw_stream(dev)),
+                   "infcl_bwd")
+            return dimg, dtxt, dscale
 
     return ClipLoss
 
