@@ -20,7 +20,9 @@
  *     INFCL_F16).  With 16-bit inputs the products run on the matching
  *     16-bit MFMA with fp32 accumulation, and the backward rounds its
  *     gradient weights (the softmax terms) to the input type, round to
- *     nearest even, before the second product; with f32 everything is fp32.
+ *     nearest even, before the second product; f32 inputs and weights enter
+ *     the products in full (each as three bf16 parts that add up to it, the
+ *     parts' products exact and accumulated in fp32).
  *     They are used exactly as given (no normalisation inside the loss).
  *   - scale: device pointer to one float, the logit scale s (1/temperature).
  *   - All float vectors are device pointers, 16-byte aligned.

@@ -23,7 +23,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libinfcl.so")
-SOURCES = ["api.hip", "fwd.hip", "fwd2.hip", "bwd.hip", "bwd_wide.hip", "ablation.hip"]
+SOURCES = ["api.hip", "fwd.hip", "fwd2.hip", "bwd.hip", "bwd_wide.hip", "bwd_f32.hip", "ablation.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -89,7 +89,7 @@ Layout make_layout(int64_t b, int64_t d, int dtype) {
   L.fwd_total = off;
   L.lse2 = off; off = align256(off + 2 * fb);
   L.bwd_part = off; off = align256(off + (size_t)2 * ((b + 63) / 64) * sizeof(double));  // 64 or 128 rows per WG
-  L.g16 = off; off = align256(off + (dtype == INFCL_F16 ? (size_t)(2 * infcl::kPrepBlocks) * sizeof(float) : 0));
+  L.g16 = off; off = align256(off + (dtype != INFCL_BF16 ? (size_t)(2 * infcl::kPrepBlocks) * sizeof(float) : 0));
   L.gpad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * sizeof(float) : 0));  // dimg, dtxt
   // partial sums: in place of the pairs, or, where those are too few, at the end
   L.part = L.pairs;

@@ -21,11 +21,10 @@
 //          registers for the whole sweep, swept rows read from LDS with a
 //          row permutation that makes the accumulator usable as GEMM2's operand)
 //   G'     two exp2 per entry (log2 domain), the diagonal from expm1 terms
-//   GEMM2  16-bit inputs: the four waves' G' blocks are exchanged through LDS and each
-//          wave multiplies all 128 own rows by its quarter of the features;
-//          fp32: each wave multiplies its own 32 rows by all features.
-// Feature widths whose accumulators do not fit the register file are split in
-// passes; each pass recomputes GEMM1.
+//   GEMM2  the four waves' G' blocks are exchanged through LDS and each wave
+//          multiplies all 128 own rows by its quarter of the features.
+// This file: 16-bit inputs, d = 128 to 512; wider rows are in bwd_wide.hip,
+// fp32 inputs in bwd_f32.hip.
 //
 // Memory pipeline.  Tiles arrive by LDS DMA (buffer loads that write LDS).
 // Each tile buffer, its log-sum-exp slot and the G' buffers are separate LDS
@@ -49,35 +48,26 @@ constexpr int kGpBytes = kBwdBM * kBwdBN * 2;  // one 16-bit G' exchange buffer
 #define INFCL_BWD_G1_PRE 4
 #endif
 
-template <typename TIN, int D, int FB, bool G16>
+template <bool F16, int D, bool G16>
 __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
-  constexpr int ES = sizeof(TIN);
-  constexpr bool F16 = std::is_same<TIN, _Float16>::value;  // fp16 (else bf16) when ES == 2
-  static_assert(ES == 2 || !G16, "16-bit gradients come with 16-bit inputs");
   using GO = GradOut<G16, F16>;  // gradient element type
   constexpr int KS = D / 16;            // 16-wide contraction steps of GEMM1
-  constexpr int ROWG = D * ES;          // bytes per row in HBM
+  constexpr int ROWG = D * 2;           // bytes per row in HBM
   constexpr int TILEB = kBwdBN * ROWG;  // bytes per swept tile
   constexpr int NIW = TILEB / 4096;     // 1 KiB DMA instructions per wave and tile
-  constexpr int FBW = ES == 2 ? FB / 4 : FB;  // 32-feature blocks per wave and pass
-  constexpr int NACC = ES == 2 ? 4 * FBW : FB;
-  constexpr int NPASS = D / (32 * FB);
-  constexpr bool PIPE = ES == 2;  // the pipelined schedule
-  static_assert(ES == 4 || NPASS == 1, "16-bit inputs: one pass");
-  constexpr int GPN = PIPE ? 2 : 0;  // G' exchange buffers
-  static_assert(D % (32 * FB) == 0, "pass width must divide d");
-  static_assert(ES == 4 || FB % 4 == 0, "16-bit pass width is a multiple of 128 features");
-  static_assert(D % 64 == 0 && KS % NIW == 0, "tile DMA layout");
-  static_assert((PIPE ? 3 : 2) * TILEB + 3 * 1024 + GPN * kGpBytes + 2048 <= 160 * 1024, "LDS budget");
+  constexpr int FBW = D / 128;          // 32-feature blocks per wave
+  constexpr int NACC = 4 * FBW;
+  static_assert(D % 128 == 0 && KS % NIW == 0, "tile DMA layout");
+  static_assert(3 * TILEB + 3 * 1024 + 2 * kGpBytes + 2048 <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char tA_[TILEB];
   __shared__ __attribute__((aligned(1024))) char tB_[TILEB];
-  __shared__ __attribute__((aligned(1024))) char tC_[PIPE ? TILEB : 16];
+  __shared__ __attribute__((aligned(1024))) char tC_[TILEB];
   // log-sum-exp slots: 32 values used; the rest of the 1 KiB catches the zeros
   // that the other lanes of the (branch-free) slot DMA write
   __shared__ __attribute__((aligned(1024))) float lA_[256];
   __shared__ __attribute__((aligned(1024))) float lB_[256];
   __shared__ __attribute__((aligned(1024))) float lC_[256];
-  __shared__ __attribute__((aligned(1024))) char gp_[GPN ? GPN * kGpBytes : 16];
+  __shared__ __attribute__((aligned(1024))) char gp_[2 * kGpBytes];
   __shared__ double red[256];
   INFCL_LDS char* const tA = (INFCL_LDS char*)tA_;
   INFCL_LDS char* const tB = (INFCL_LDS char*)tB_;
@@ -101,7 +91,6 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   const int64_t iown = own0 + l32;                                 // this lane's own row
   const bool own_ok = iown < p.own_end;
   const int64_t irow = own_ok ? iown : p.own_end - 1;
-  const bool wave_rows_ok = own0 + 32 <= p.own_end;
   const int own0_t = (int)(own0 - task.row0);  // counted from the first swept row
 
   const float s = p.scale[0];
@@ -113,15 +102,11 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   const float kfin = dl * s / (2.0f * (float)b) * (F16 ? ldexpf(1.f, -g16e) : 1.0f);
 
   // own operand of GEMM1, held for the whole sweep: row irow, slots 8h..8h+7 of each step
-  typedef typename std::conditional<ES == 2, bf16x8, f32x4>::type frag_t;
-  constexpr int FR = ES == 2 ? 1 : 2;  // 16-byte loads per step and lane
-  frag_t ownf[KS][FR];
+  bf16x8 ownf[KS];
   {
-    const char* src = (const char*)sd.own + (irow * D) * ES;
+    const __bf16* src = (const __bf16*)sd.own + irow * D + 8 * h;
 #pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2)
-#pragma unroll
-      for (int u = 0; u < FR; ++u) ownf[s2][u] = *(const frag_t*)(src + (16 * s2 + 8 * h) * ES + 16 * u);
+    for (int s2 = 0; s2 < KS; ++s2) ownf[s2] = *(const bf16x8*)(src + 16 * s2);
   }
   const float aO = own_ok ? sd.lse_own[iown] * kLog2e : 0.f;
   const float uO = own_ok ? p.udiag[iown] : 0.f;
@@ -172,7 +157,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
     const int l32o = lo & 31, ho = lo >> 5;
     const int rA = sweep_perm(l32o);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) offA[k] = sweep_seg_off(rA, ES == 2 ? (2 * k + ho) : (4 * (k >> 1) + 2 * ho + (k & 1)));
+    for (int k = 0; k < 8; ++k) offA[k] = sweep_seg_off(rA, 2 * k + ho);
   };
 
   double ds_acc = 0.0;
@@ -181,21 +166,12 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
   // LDS fragments are read kPre steps ahead of their MFMA through a register
   // ring.  With with_dma, the loads of tile dtile into (ddst, dlse) are issued
   // between the MFMAs, one 1 KiB instruction per KS / NIW steps.
-  // 16-bit inputs: GEMM1's fragment offsets are computed once and held in
-  // registers (rebuilt per tile they cost about 2.5% of the backward at
-  // d = 512; the fp32 form has no registers to spare and rebuilds them)
-  constexpr bool HA = ES == 2;
-  int offA_h[8];
-  if constexpr (HA) make_offA(lane, offA_h);
+  // GEMM1's fragment offsets are computed once and held in registers (rebuilt
+  // per tile they cost about 2.5% of the backward at d = 512)
+  int offA[8];
+  make_offA(lane, offA);
   auto gemm1 = [&](const INFCL_LDS char* cur, bool with_dma, int dtile, INFCL_LDS char* ddst,
                    INFCL_LDS float* dlse) {
-    int offA[8];
-    if constexpr (HA) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) offA[k] = offA_h[k];
-    } else {
-      make_offA(opaque_lane(), offA);
-    }
     u32x4 drs = tile_rsrc(0), drl = lse_rsrc(0);
     uint32_t dlo = 0;
     if (with_dma) {
@@ -213,37 +189,21 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       if (s2 == (KS > 1 ? 1 : 0)) dma16_asm(drl, dlse, lse_lane_off());
     };
     f32x16 sacc;
-    if constexpr (ES == 2) {
-      constexpr int kPre = KS < INFCL_BWD_G1_PRE ? KS : INFCL_BWD_G1_PRE;
-      bf16x8 ring[kPre];
+    constexpr int kPre = KS < INFCL_BWD_G1_PRE ? KS : INFCL_BWD_G1_PRE;
+    bf16x8 ring[kPre];
 #pragma unroll
-      for (int i = 0; i < kPre; ++i) ring[i] = *(const INFCL_LDS bf16x8*)(cur + offA[i & 7] + kSeg * (i >> 3));
-      __builtin_amdgcn_sched_group_barrier(0x100, kPre, 0);
+    for (int i = 0; i < kPre; ++i) ring[i] = *(const INFCL_LDS bf16x8*)(cur + offA[i & 7] + kSeg * (i >> 3));
+    __builtin_amdgcn_sched_group_barrier(0x100, kPre, 0);
 #pragma unroll
-      for (int s2 = 0; s2 < KS; ++s2) {
-        // no leading padding (its sources are LDS loads and the own
-        // rows, never restored just before; the build's scan checks it)
-        mfma16_vgpr<F16, false>(sacc, ring[s2 % kPre], ownf[s2][0], s2 == 0, s2 == KS - 1);
-        dma_step(s2);
-        if (s2 + kPre < KS) {
-          const int n = s2 + kPre;
-          ring[s2 % kPre] = *(const INFCL_LDS bf16x8*)(cur + offA[n & 7] + kSeg * (n >> 3));
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
-#pragma unroll
-      for (int s2 = 0; s2 < KS; ++s2) {
-        const int kb = 2 * (s2 & 3);
-        f32x4 a0 = *(const INFCL_LDS f32x4*)(cur + offA[kb] + kSeg * (s2 >> 2));
-        f32x4 a1 = *(const INFCL_LDS f32x4*)(cur + offA[kb + 1] + kSeg * (s2 >> 2));
-#pragma unroll
-        for (int t = 0; t < 4; ++t) sacc = mfma_f32(a0[t], ownf[s2][0][t], sacc);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) sacc = mfma_f32(a1[t], ownf[s2][1][t], sacc);
-        dma_step(s2);
+    for (int s2 = 0; s2 < KS; ++s2) {
+      // no leading padding (its sources are LDS loads and the own
+      // rows, never restored just before; the build's scan checks it)
+      mfma16_vgpr<F16, false>(sacc, ring[s2 % kPre], ownf[s2], s2 == 0, s2 == KS - 1);
+      dma_step(s2);
+      if (s2 + kPre < KS) {
+        const int n = s2 + kPre;
+        ring[s2 % kPre] = *(const INFCL_LDS bf16x8*)(cur + offA[n & 7] + kSeg * (n >> 3));
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
     }
     return sacc;
@@ -303,28 +263,24 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       *(INFCL_LDS bf16x8*)(gpb + gp_chunk_off(row, 2 * s2 + (lo >> 5))) = ga[s2];
   };
 
-  // 16-bit: GEMM2's per-lane offsets, computed once: another 2.5% at d = 512
-  constexpr bool HB = ES == 2;
+  // GEMM2's per-lane offsets, computed once: another 2.5% at d = 512
   int offBh[2][FBW], offGh[2];
-  if constexpr (HB) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int fbw = 0; fbw < FBW; ++fbw) offBh[t][fbw] = sweep_tr_off(lane, t, wave * FBW + fbw);
+    for (int fbw = 0; fbw < FBW; ++fbw) offBh[t][fbw] = sweep_tr_off(lane, t, wave * FBW + fbw);
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) offGh[s2] = gp_chunk_off(l32, 2 * s2 + h);
-  }
-  for (int pass = 0; pass < NPASS; ++pass) {
-    // 16-bit: dacc[ob * FBW + fbw] holds own block ob (rows 32 ob .. of the
-    // workgroup) x feature block (pass FB + wave FBW + fbw).
-    // fp32: dacc[fb] holds this wave's own rows x feature block (pass FB + fb).
+  for (int s2 = 0; s2 < 2; ++s2) offGh[s2] = gp_chunk_off(l32, 2 * s2 + h);
+  {
+    // dacc[ob * FBW + fbw] holds own block ob (rows 32 ob .. of the workgroup)
+    // x feature block wave FBW + fbw
     f32x16 dacc[NACC];
 #pragma unroll
     for (int i = 0; i < NACC; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) dacc[i][r] = 0.f;
 
-    // ---- 16-bit GEMM2 of the tile in cur with the G' in gpb, as an explicit
+    // ---- GEMM2 of the tile in cur with the G' in gpb, as an explicit
     // software pipeline over its 2 FBW groups (contraction half s2, feature
     // block fbw; 4 MFMAs each, one per own block): stage g issues the LDS reads
     // of group g + 2 and then the MFMAs of group g.  The stages also
@@ -395,23 +351,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
       return ds_tile;
     };
 
-    // ---- fp32 GEMM2: this wave's own rows x all the pass's features; step r
-    // contracts swept row jr(r, h) of each lane half.
-    auto gemm2_f32 = [&](const INFCL_LDS char* cur, const float (&gv)[16]) {
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb) {
-        const int fbabs = pass * FB + fb;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = sweep_perm(8 * (r >> 2) + 4 * h + (r & 3));
-          const int cf = 8 * fbabs + (l32 >> 2);
-          float bv = *(const INFCL_LDS float*)(cur + sweep_chunk_off(j, cf) + (l32 & 3) * 4);
-          dacc[fb] = mfma_f32(gv[r], bv, dacc[fb]);
-        }
-      }
-    };
-
-    if constexpr (PIPE) {
+    {
       // Software pipeline over tiles: iteration jt runs GEMM1 of tile jt+1
       // (issuing the loads of tile jt+2), then GEMM2 of tile jt together with
       // the G' of tile jt+1.  Three tile buffers rotate; G' buffers alternate.
@@ -425,7 +365,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         const f32x16 sacc = gemm1(tA, false, 0, tC, lC);
         float gv[16];
         const float d0 = epilogue(0, lA, sacc, gv);
-        if (pass == 0) ds_acc += (double)d0;
+        ds_acc += (double)d0;
         bf16x8 ga[2];
         to_h16(gv, ga);
         put_gp(gp, ga);
@@ -447,7 +387,7 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
           dn = epilogue(jt + 1, lnxt, sacc, gv);
           to_h16(gv, ga);
         }
-        if (pass == 0 && next) ds_acc += (double)dn;
+        if (next) ds_acc += (double)dn;
         put_gp(gp + ((jt + 1) & 1) * kGpBytes, ga);
         wait_dma();
         __syncthreads();
@@ -459,79 +399,35 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         body(jt + 1, tB, tC, lC, tA, lA);
         body(jt + 2, tC, tA, lA, tB, lB);
       }
-    } else {
-      // fp32: two tile buffers, GEMM1 of tile jt (issuing the loads of tile jt+1),
-      // G', GEMM2.
-      issue_tile(0, tA, lA);
-      wait_dma();
-      __syncthreads();
-      auto body = [&](int jt, const INFCL_LDS char* cur, const INFCL_LDS float* lcur, INFCL_LDS char* nxt,
-                      INFCL_LDS float* lnxt) {
-        const f32x16 sacc = gemm1(cur, true, jt + 1, nxt, lnxt);
-        float gv[16];
-        const float d0 = epilogue(jt, lcur, sacc, gv);
-        if (pass == 0) ds_acc += (double)d0;
-        gemm2_f32(cur, gv);
-        wait_dma();
-        __syncthreads();
-      };
-      // Unrolled over the buffer pair without a test in between: a tile
-      // index past the end is a tile of rows past the end, fully masked (zero G').
-      for (int jt = 0; jt < ntile; jt += 2) {
-        body(jt, tA, lA, tB, lB);
-        body(jt + 1, tB, lB, tA, lA);
-      }
     }
 
     // ---- write dOwn (or this part's unscaled sums): lane holds feature l32 of
     // a 32-feature block, rows 8(r>>2)+4h+(r&3)
-    if constexpr (ES == 2) {
-      const int rl0 = 4 * h, f0 = 32 * (pass * FB + wave * FBW) + l32;
-      if (task.part) {
+    const int rl0 = 4 * h, f0 = 32 * wave * FBW + l32;
+    if (task.part) {
 #pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-          float* dst = task.part + (32 * ob + rl0) * D + f0;
+      for (int ob = 0; ob < 4; ++ob) {
+        float* dst = task.part + (32 * ob + rl0) * D + f0;
 #pragma unroll
-          for (int fbw = 0; fbw < FBW; ++fbw)
+        for (int fbw = 0; fbw < FBW; ++fbw)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = dacc[ob * FBW + fbw][r];
-        }
-      } else {
-        const bool all_ok = wg0 + kBwdBM <= p.own_end;
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-          auto* dst = (typename GO::type*)sd.dOwn + (wg0 - p.own_off + 32 * ob + rl0) * D + f0;
-#pragma unroll
-          for (int fbw = 0; fbw < FBW; ++fbw)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int64_t row = wg0 + 32 * ob + 8 * (r >> 2) + rl0 + (r & 3);
-              if (all_ok || row < p.own_end)
-                dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[ob * FBW + fbw][r]);
-            }
-        }
+          for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = dacc[ob * FBW + fbw][r];
       }
     } else {
-      const int f0 = 32 * pass * FB + l32;
-      if (task.part) {
-        float* dst = task.part + (32 * wave + 4 * h) * D + f0;
+      const bool all_ok = wg0 + kBwdBM <= p.own_end;
 #pragma unroll
-        for (int fb = 0; fb < FB; ++fb)
+      for (int ob = 0; ob < 4; ++ob) {
+        auto* dst = (typename GO::type*)sd.dOwn + (wg0 - p.own_off + 32 * ob + rl0) * D + f0;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fb] = dacc[fb][r];
-      } else {
-        auto* dst = (typename GO::type*)sd.dOwn + (own0 - p.own_off + 4 * h) * D + f0;
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb)
+        for (int fbw = 0; fbw < FBW; ++fbw)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int64_t row = own0 + 8 * (r >> 2) + 4 * h + (r & 3);
-            if (wave_rows_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fb] = GO::cvt(kfin * dacc[fb][r]);
+            const int64_t row = wg0 + 32 * ob + 8 * (r >> 2) + rl0 + (r & 3);
+            if (all_ok || row < p.own_end)
+              dst[(8 * (r >> 2) + (r & 3)) * D + 32 * fbw] = GO::cvt(kfin * dacc[ob * FBW + fbw][r]);
           }
       }
     }
-    // the next pass reuses the tile buffers
-    __syncthreads();
   }
 
   // ---- dscale partial of this workgroup: fixed-order reduction
@@ -575,7 +471,7 @@ __global__ void __launch_bounds__(256) dscale_finish(const double* part, int64_t
 // lane; at most 64 MiB of them, which stay in the last-level cache: 12 us).
 // One more workgroup (the last grid row) sums dscale: as a launch of its own
 // that took 4.7 us.
-template <bool G16, bool F16>
+template <bool G16, bool F16, bool SC = F16>
 __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, float* dscale, double* dscale64) {
   using GO = GradOut<G16, F16>;
   if (blockIdx.y == gridDim.y - 1) {
@@ -592,7 +488,7 @@ __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, 
   const int64_t row = (int64_t)(sd ? blk - p.nblk : blk) * bm + rl;  // own row - own_off
   const float s = p.scale[0];
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  const float kfin = dl * s / (2.0f * (float)p.b) * (F16 ? ldexpf(1.f, -g16_exponent(p.g16)) : 1.0f);
+  const float kfin = dl * s / (2.0f * (float)p.b) * (SC ? ldexpf(1.f, -g16_exponent(p.g16)) : 1.0f);
   if (e >= per || row >= p.own_end - p.own_off) return;
   const f32x4* src = (const f32x4*)(p.part + (int64_t)q * p.ns * per * 4) + e;
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
@@ -612,59 +508,21 @@ __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, 
   *(out4*)((typename GO::type*)p.side[sd].dOwn + row * p.d + 4 * (e - rl * c4)) = o;
 }
 
-// Pass width: largest FB (32-feature blocks) dividing d/32 whose accumulators
-// (16 FB registers) fit next to the own operand (d/4 or d/2 registers); for
-// 16-bit inputs FB is also a multiple of 4 (see the transposing-read addressing).
-// Build-time tuning knob: the register budget shared by the own operand and
-// the gradient accumulators.
-#ifndef INFCL_BWD_REG_BUDGET
-#define INFCL_BWD_REG_BUDGET 384
-#endif
-template <typename TIN, int D>
-static int launch_bwd_d(const BwdParams& p, int nwg, hipStream_t stream) {
-  constexpr int ES = sizeof(TIN);
-  constexpr int OWNREGS = D * ES / 8;
-  constexpr int NB32 = D / 32;
-  constexpr int FBMAX = (INFCL_BWD_REG_BUDGET - OWNREGS) / 16;
-  constexpr int FB = [] {
-    int best = ES == 4 ? 1 : 4;  // 16-bit: at least one 128-feature group
-    for (int f = 1; f <= NB32; ++f)
-      if (NB32 % f == 0 && f <= FBMAX && (ES == 4 || f % 4 == 0)) best = f;
-    return best;
-  }();
-  static_assert(ES == 4 || FB % 4 == 0, "16-bit pass width must be a multiple of 128 features");
-  if constexpr (ES == 2) {
-    if (p.gdt) {
-      hipLaunchKernelGGL((bwd_sweep<TIN, D, FB, true>), dim3(nwg), dim3(256), 0, stream, p);
-      return hipGetLastError() == hipSuccess ? 0 : 1;
-    }
-  }
-  hipLaunchKernelGGL((bwd_sweep<TIN, D, FB, false>), dim3(nwg), dim3(256), 0, stream, p);
-  return hipGetLastError() == hipSuccess ? 0 : 1;
-}
-
-template <typename TIN>
-static int launch_bwd_t(const BwdParams& p, int nwg, hipStream_t stream) {
-  const int64_t d = p.d;
-  if constexpr (sizeof(TIN) == 2) {
-    switch (d) {
-      case 128: return launch_bwd_d<TIN, 128>(p, nwg, stream);
-      case 256: return launch_bwd_d<TIN, 256>(p, nwg, stream);
-      case 384: return launch_bwd_d<TIN, 384>(p, nwg, stream);
-      case 512: return launch_bwd_d<TIN, 512>(p, nwg, stream);
-      // wider rows take the wide-row sweep
-    }
-  } else {
-    switch (d) {
-      case 64: return launch_bwd_d<TIN, 64>(p, nwg, stream);
-      case 128: return launch_bwd_d<TIN, 128>(p, nwg, stream);
-      case 192: return launch_bwd_d<TIN, 192>(p, nwg, stream);
-      case 256: return launch_bwd_d<TIN, 256>(p, nwg, stream);
-      case 320: return launch_bwd_d<TIN, 320>(p, nwg, stream);
-      case 384: return launch_bwd_d<TIN, 384>(p, nwg, stream);
-      case 448: return launch_bwd_d<TIN, 448>(p, nwg, stream);
-      case 512: return launch_bwd_d<TIN, 512>(p, nwg, stream);
-    }
+template <bool F16>
+static int launch_bwd_sweep(const BwdParams& p, int nwg, hipStream_t stream) {
+  auto go = [&](auto dc) {
+    constexpr int D = decltype(dc)::value;
+    if (p.gdt)
+      hipLaunchKernelGGL((bwd_sweep<F16, D, true>), dim3(nwg), dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL((bwd_sweep<F16, D, false>), dim3(nwg), dim3(256), 0, stream, p);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+  };
+  switch (p.d) {
+    case 128: return go(std::integral_constant<int, 128>{});
+    case 256: return go(std::integral_constant<int, 256>{});
+    case 384: return go(std::integral_constant<int, 384>{});
+    case 512: return go(std::integral_constant<int, 512>{});
   }
   return 2;
 }
@@ -705,6 +563,7 @@ __global__ void __launch_bounds__(256) bwd_prep(const float* lse_r, const float*
 
 bool bwd_wide_supported(int64_t d, int dtype);
 int launch_bwd_wide(const BwdParams& p, int nwg, bool f16, hipStream_t stream);
+int launch_bwd_f32(const BwdParams& p, int nwg, hipStream_t stream);
 
 // Split of the backward over workgroups, for nrows own rows of each side
 // against b swept rows: both sides' row blocks run in one launch, and the
@@ -728,7 +587,7 @@ BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
   const int rem = total - pl.nfull;
   if (rem > 0) {
     // microseconds: a tile, a part's fixed cost, a part's bytes through the reduction
-    const double t_tile = dtype == 1 ? 2.0e-5 * (double)(d * d) + 0.02 * (double)d : 3.7e-3 * (double)d;
+    const double t_tile = (dtype == 1 ? 0.011 : 3.7e-3) * (double)d;
     const double blk_bytes = (double)pl.bm * (double)d * 4.0;
     double best = 0.0;
     for (int ns = 1; ns <= 64 && ns <= ntile; ++ns) {
@@ -754,8 +613,8 @@ BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
   return pl;
 }
 
-// Backward: 16-bit inputs with d >= 640 take the single-pass wide-row sweep
-// (64 own rows per workgroup), everything else the 128-row sweep above.  Own
+// Backward: 16-bit inputs take the 128-row sweep above up to d = 512 and the
+// wide-row sweeps (64 own rows per workgroup) beyond; fp32 inputs have their own.  Own
 // rows are [r0, r0 + nrows) of both sides (all b for the whole batch; a
 // shard's samples otherwise, with dimg/dtxt [nrows, d]: fp32, or with gdt = 1
 // the 16-bit input type); lse_r, lse_c and aux cover all b samples.  dscale
@@ -770,7 +629,7 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
   float* l2r = lse2;
   float* l2c = lse2 + b;
   hipLaunchKernelGGL(bwd_prep, dim3(kPrepBlocks), dim3(256), 0, stream, lse_r, lse_c, aux, l2r, l2c,
-                     dtype == 2 ? g16 : nullptr, b);
+                     dtype != 0 ? g16 : nullptr, b);
   if (hipGetLastError() != hipSuccess) return 1;
   BwdParams p;
   p.g16 = g16;
@@ -791,14 +650,14 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
   const int64_t split = 2 * (int64_t)pl.nblk - pl.nfull;  // split row blocks
   p.ds_part = pl.ns > 1 ? (double*)(part + split * pl.ns * pl.bm * d) : ds_part;
   int rc;
-  if (wide)
+  if (dtype == 1)
+    rc = launch_bwd_f32(p, pl.nwg, stream);
+  else if (wide)
     rc = launch_bwd_wide(p, pl.nwg, dtype == 2, stream);
-  else if (dtype == 0)
-    rc = launch_bwd_t<__bf16>(p, pl.nwg, stream);
   else if (dtype == 2)
-    rc = launch_bwd_t<_Float16>(p, pl.nwg, stream);
+    rc = launch_bwd_sweep<true>(p, pl.nwg, stream);
   else
-    rc = launch_bwd_t<float>(p, pl.nwg, stream);
+    rc = launch_bwd_sweep<false>(p, pl.nwg, stream);
   if (rc) return rc;
   if (pl.ns > 1) {
     const dim3 grid((unsigned)((pl.bm * (d >> 2) + 255) / 256), (unsigned)split + 1);
@@ -807,6 +666,9 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
                          dscale64);
     else if (dtype == 2)
       hipLaunchKernelGGL((bwd_reduce<false, true>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,
+                         dscale64);
+    else if (dtype == 1)
+      hipLaunchKernelGGL((bwd_reduce<false, false, true>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,
                          dscale64);
     else if (gdt)
       hipLaunchKernelGGL((bwd_reduce<true, false>), grid, dim3(256), 0, stream, p, pl.bm, pl.nwg, dscale,

@@ -718,9 +718,7 @@ __global__ void __launch_bounds__(256, 1) bwd_wide3(BwdParams p) {
   if (threadIdx.x == 0) p.ds_part[blockIdx.x] = red[0];
 }
 
-bool bwd_wide_supported(int64_t d, int dtype) { 
-  return (dtype == 0 || dtype == 2) && (d == 640 || d == 768 || d == 896 || d == 1024);
-}
+bool bwd_wide_supported(int64_t d, int dtype) { return dtype == 1 || d >= 640; }
 
 int launch_bwd_wide(const BwdParams& p, int nwg, bool f16, hipStream_t stream) {
   auto go = [&](auto f16c, auto g16c) {

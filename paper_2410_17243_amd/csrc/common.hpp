@@ -1,8 +1,8 @@
 // Shared device helpers for the tiled contrastive-loss kernels (gfx950 only).
 //
 // Conventions used by both sweeps
-//   - Matrix products run on the 32x32x16 bf16 or fp16 MFMA (fp32 accumulate)
-//     or the 32x32x2 fp32 MFMA.  Fragments of both 16-bit types are carried
+//   - Matrix products run on the 32x32x16 bf16 or fp16 MFMA (fp32 accumulate),
+//     those of fp32 inputs as six products of bf16 parts (split3).  Fragments of both 16-bit types are carried
 //     in bf16x8 registers; only the MFMA opcode and the conversions differ.  For a 32x32 output block, lane L holds column
 //     n = L % 32 and rows m = 8*(r/4) + 4*(L/32) + r%4 for accumulator r = 0..15.
 //     Operand fragments: lane L holds row L % 32 and the 8 consecutive
@@ -67,8 +67,54 @@ __device__ __forceinline__ float from16(__bf16 x) {
   else
     return (float)x;
 }
-__device__ __forceinline__ f32x16 mfma_f32(float a, float b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+// An fp32 operand fragment as three bf16 fragments, x = p0 + p1 + p2: each
+// part is the remainder so far rounded to nearest, and the remainders are exact,
+// so the parts carry x's 24 bits (8 + 8 + 8, with the signs).  A product of two
+// such operands is six bf16 MFMAs (mfma_split): the three products left out,
+// p1 q2, p2 q1 and p2 q2, are below 2^-25 of the full one, less than fp32's own
+// rounding of it, and every bf16 product is exact in the fp32 accumulator.  Six
+// 32x32x16 bf16 MFMAs take 192 cycles where eight 32x32x2 fp32 ones take 512.
+struct split3 {
+  bf16x8 p[3];
+};
+// two floats to packed bf16 (one v_cvt_pk_bf16_f32), round to nearest even
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// one pair of values into element pair e of the three parts; eleven instructions
+__device__ __forceinline__ void split_pair(float u, float v, int e, u32x4 (&p)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t q = pk_bf16(u, v);
+    p[k][e] = q;
+    u -= __uint_as_float(q << 16);
+    v -= __uint_as_float(q & 0xFFFF0000u);
+  }
+}
+__device__ __forceinline__ split3 split_f32(const float (&x)[8]) {
+  u32x4 p[3];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) split_pair(x[2 * e], x[2 * e + 1], e, p);
+  split3 s;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s.p[k] = __builtin_bit_cast(bf16x8, p[k]);
+  return s;
+}
+__device__ __forceinline__ split3 split_f32(f32x4 lo, f32x4 hi) {
+  const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return split_f32(x);
+}
+// c0 + c1 += a b, in two independent accumulation chains
+__device__ __forceinline__ void mfma_split(const split3& a, const split3& b, f32x16& c0, f32x16& c1) {
+  c0 = mfma_bf16(a.p[2], b.p[0], c0);
+  c1 = mfma_bf16(a.p[0], b.p[2], c1);
+  c0 = mfma_bf16(a.p[1], b.p[1], c0);
+  c1 = mfma_bf16(a.p[1], b.p[0], c1);
+  c0 = mfma_bf16(a.p[0], b.p[1], c0);
+  c1 = mfma_bf16(a.p[0], b.p[0], c1);
 }
 
 // Asynchronous 16-byte global -> LDS copy.  Lane L writes LDS bytes

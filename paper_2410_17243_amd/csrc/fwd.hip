@@ -9,9 +9,13 @@
 // Work decomposition (differs from the paper's one-row-block-per-thread-block
 // design: here a persistent 2-D grid of workgroups shares the column
 // statistics without atomics):
-//   - A workgroup tile covers BI = 64 rows i (image rows) x BJ = 256 columns j
-//     (text rows).  The MFMA computes the transposed block S^T (M = j, N = i),
-//     so each lane owns a fixed i and 16 consecutive-ish j's per 32x32 block.
+//   - A workgroup tile covers 64 rows i (image rows) x 256 columns j (text
+//     rows), or 32 x 128 where few tiles would leave compute units idle.  The
+//     MFMA computes the transposed block S^T (M = j, N = i), so each lane owns a
+//     fixed i and 16 consecutive-ish j's per 32x32 block.
+//   - The products run on the bf16 MFMA, every fp32 operand in three exact
+//     bf16 parts (split3 in common.hpp): b = 8192, d = 512 558 -> 423 us against
+//     the fp32 MFMA, d = 256 310 -> 234 us, at a smaller error.
 //   - Workgroup (q, g) of a P_r x P_c grid sweeps row tiles q, q+P_r, ... and,
 //     for each, the column tiles of column group g.  Row statistics stay in
 //     registers across the sweep (one running pair per lane and row, merged
@@ -42,17 +46,23 @@ struct FwdParams {
   float* rowL;
   float* colR;  // [Pr][b]       per row group partial column pairs
   float* colL;
-  float* udiag;  // [b]  <img_i, txt_i> as accumulated by the MFMA
+  float* udiag;  // [b]  <img_i, txt_i>
   int Pr, Pc;
   int nRT, nCT;
   int64_t r0, rend;  // own rows [r0, rend) (a shard of the batch; 0 and b for the whole batch)
   int64_t rstride;   // rend - r0
 };
 
-constexpr int kFwdBI = 64;    // rows i per workgroup tile
-constexpr int kFwdBJ = 256;   // columns j per workgroup tile
-constexpr int kFwdRows = kFwdBI + kFwdBJ;
-constexpr int kFwdStageBytes = kFwdRows * 128;  // 128 bytes of every row per stage
+// Shape of a workgroup tile: MB 32-column blocks per wave (four waves), NB
+// 32-row blocks; 128 bytes of every row per stage.
+template <int MB, int NB>
+struct FwdTile {
+  static constexpr int BI = 32 * NB;   // rows i
+  static constexpr int BJ = 128 * MB;  // columns j
+  static constexpr int Rows = BI + BJ;
+  static constexpr int StageBytes = Rows * 128;
+  static constexpr int NIW = Rows / 32;  // 1 KiB DMA instructions per wave and stage
+};
 
 // Chunk swizzle for 128-byte rows: 16 consecutive rows reading the same logical
 // 16-byte chunk hit 16 distinct bank groups.
@@ -60,71 +70,75 @@ __device__ __forceinline__ int fwd_swz(int r, int c) { return c ^ ((r >> 1) & 7)
 
 // Per-lane source offsets of the K-stage DMA: instruction k (= wave + 4 kk)
 // fills tile rows 8k..8k+7; lane L copies logical chunk fwd_swz(r, L & 7) of row
-// r = 8k + L/8 to physical chunk L & 7.  Rows 0..63 are image rows, 64..319 text rows.
+// r = 8k + L/8 to physical chunk L & 7.  The first BI rows are image rows, the others text rows.
+template <int NIW>
 struct FwdDmaOffsets {
-  uint32_t off[kFwdRows / 8 / 4];
+  uint32_t off[NIW];
 };
 
-__device__ __forceinline__ FwdDmaOffsets fwd_dma_offsets(int64_t d, int es, int wave, int lane) {
-  FwdDmaOffsets o;
+template <int MB, int NB>
+__device__ __forceinline__ FwdDmaOffsets<FwdTile<MB, NB>::NIW> fwd_dma_offsets(int64_t d, int es, int wave, int lane) {
+  using T = FwdTile<MB, NB>;
+  FwdDmaOffsets<T::NIW> o;
 #pragma unroll
-  for (int kk = 0; kk < kFwdRows / 8 / 4; ++kk) {
+  for (int kk = 0; kk < T::NIW; ++kk) {
     const int k = wave + 4 * kk;
     const int r = 8 * k + (lane >> 3);
-    const int rl = kk < 2 ? r : r - kFwdBI;  // row within the image or the text tile
+    const int rl = kk < NB ? r : r - T::BI;  // row within the image or the text tile
     o.off[kk] = (uint32_t)(rl * d * es + 16 * fwd_swz(r, lane & 7));
   }
   return o;
 }
 
-// Issue the DMA of one K-stage (128 bytes of each of the 320 tile rows).  Rows
+// Issue the DMA of one K-stage (128 bytes of each of the tile's rows).  Rows
 // past b fall outside the buffer resources and load as zeros (they are masked).
-__device__ __forceinline__ void fwd_stage_dma(const FwdParams& p, const FwdDmaOffsets& o, int64_t i0, int64_t j0,
-                                              int st, INFCL_LDS char* buf, int wave) {
+template <int MB, int NB>
+__device__ __forceinline__ void fwd_stage_dma(const FwdParams& p, const FwdDmaOffsets<FwdTile<MB, NB>::NIW>& o,
+                                              int64_t i0, int64_t j0, int st, INFCL_LDS char* buf, int wave) {
   const int64_t b = p.b, rowb = p.d * (int64_t)sizeof(float);
   const u32x4 ri = rsrc_words((const char*)p.img + i0 * rowb, (p.rend - i0) * rowb);
   const u32x4 rt = rsrc_words((const char*)p.txt + j0 * rowb, (b - j0) * rowb);
   const uint32_t soff = (uint32_t)st * 128u;
 #pragma unroll
-  for (int kk = 0; kk < kFwdRows / 8 / 4; ++kk)
-    dma16_asm(kk < 2 ? ri : rt, buf + 1024 * (wave + 4 * kk), o.off[kk], soff);
+  for (int kk = 0; kk < FwdTile<MB, NB>::NIW; ++kk)
+    dma16_asm(kk < NB ? ri : rt, buf + 1024 * (wave + 4 * kk), o.off[kk], soff);
 }
 
 // MFMA work of one K-stage: acc[mb][nb] += S^T block (j block mb, i block nb).
-// A 16-wide fp32 contraction step is 64 bytes; lane half h holds floats 8h..8h+7.
-__device__ __forceinline__ void fwd_stage_mfma(const INFCL_LDS char* buf, f32x16 (&acc)[2][2], int wave, int lane) {
+// A 16-wide contraction step is 64 bytes; lane half h holds floats 8h..8h+7.
+// The products run on the bf16 MFMA with every operand in three exact bf16
+// parts (split3): 24 MFMAs of 32 cycles per step and wave instead of 32 of 64,
+// next to 176 vector instructions that split the fragments (two waves share a
+// SIMD, so one's splitting overlaps the other's MFMAs).
+template <int MB, int NB>
+__device__ __forceinline__ void fwd_stage_mfma(const INFCL_LDS char* buf, f32x16 (&acc)[MB][NB], int wave, int lane) {
   const int l32 = lane & 31, h = lane >> 5;
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    f32x4 a[2][2], bb[2][2];
+    split3 a[MB], bb[NB];
+    auto frag = [&](int r) {
+      const int c = 4 * s + 2 * h;
+      return split_f32(*(const INFCL_LDS f32x4*)(buf + r * 128 + fwd_swz(r, c) * 16),
+                       *(const INFCL_LDS f32x4*)(buf + r * 128 + fwd_swz(r, c + 1) * 16));
+    };
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = 4 * s + 2 * h + u;
+    for (int mb = 0; mb < MB; ++mb) a[mb] = frag(FwdTile<MB, NB>::BI + 32 * MB * wave + 32 * mb + l32);
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        int r = kFwdBI + 64 * wave + 32 * mb + l32;
-        a[mb][u] = *(const INFCL_LDS f32x4*)(buf + r * 128 + fwd_swz(r, c) * 16);
-      }
+    for (int nb = 0; nb < NB; ++nb) bb[nb] = frag(32 * nb + l32);
+    constexpr int qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        int r = 32 * nb + l32;
-        bb[nb][u] = *(const INFCL_LDS f32x4*)(buf + r * 128 + fwd_swz(r, c) * 16);
-      }
-    }
+    for (int t = 0; t < 6; ++t)
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-          acc[mb][nb] = mfma_f32(a[mb][t >> 2][t & 3], bb[nb][t >> 2][t & 3], acc[mb][nb]);
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma_bf16(a[mb].p[qa[t]], bb[nb].p[qb[t]], acc[mb][nb]);
   }
 }
 
 // One butterfly step of the reduce-scatter below: lanes exchange the half of
 // their HALF*2 live values that the partner keeps (partner = lane ^ HALF).
-template <bool kMax, int HALF>
-__device__ __forceinline__ void rs_step(float (&v)[32], int l32) {
+template <bool kMax, int HALF, int N>
+__device__ __forceinline__ void rs_step(float (&v)[N], int l32) {
   const bool bit = (l32 & HALF) != 0;
 #pragma unroll
   for (int t = 0; t < HALF; ++t) {
@@ -136,51 +150,64 @@ __device__ __forceinline__ void rs_step(float (&v)[32], int l32) {
 }
 
 // Reduce-scatter over the 32 lanes of each wave half: on entry v[t] is this
-// lane's partial for value index t (0..31); on exit the result is the total over
-// the 32 lanes for index t = lane % 32 (sum, or max when kMax).
-template <bool kMax>
-__device__ __forceinline__ float half_reduce_scatter(float (&v)[32], int lane) {
+// lane's partial for value index t (0..N-1, N = 32 or 16); on exit the result
+// is the total over the 32 lanes for index fwd_rs_index<N>(lane) (sum, or max
+// when kMax); with N = 16 lanes l and l ^ 8 hold the same one.
+template <int N>
+__device__ __forceinline__ int fwd_rs_index(int l32) {
+  return N == 32 ? l32 : ((l32 >> 4) << 3) | (l32 & 7);
+}
+template <int N>
+__device__ __forceinline__ int fwd_rs_lane(int t) {
+  return N == 32 ? t : ((t >> 3) << 4) | (t & 7);
+}
+template <bool kMax, int N>
+__device__ __forceinline__ float half_reduce_scatter(float (&v)[N], int lane) {
   const int l32 = lane & 31;
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
+  for (int t = 0; t < N / 2; ++t) {
     // odd 16-lane rows of x swap with even rows of y: lanes with bit 4 clear end
-    // with (own v[t], partner v[t]); lanes with bit 4 set with (partner v[t+16], own v[t+16])
-    auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[t]), __float_as_uint(v[t + 16]), false, false);
+    // with (own v[t], partner v[t]); lanes with bit 4 set with (partner v[t+N/2], own v[t+N/2])
+    auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[t]), __float_as_uint(v[t + N / 2]), false, false);
     const float x = __uint_as_float(sw[0]), y = __uint_as_float(sw[1]);
     v[t] = kMax ? fmaxf(x, y) : x + y;
   }
-  rs_step<kMax, 8>(v, l32);
+  if constexpr (N == 32) rs_step<kMax, 8>(v, l32);
   rs_step<kMax, 4>(v, l32);
   rs_step<kMax, 2>(v, l32);
   rs_step<kMax, 1>(v, l32);
+  if constexpr (N == 16) {
+    const float o = shfl_xor(v[0], 8);
+    v[0] = kMax ? fmaxf(v[0], o) : v[0] + o;
+  }
   return v[0];
 }
 
 // Epilogue of one workgroup tile.  acc[mb][nb][r] <-> column
-// j = jw + 32 mb + 8 (r>>2) + (r&3), row i = i0 + 32 nb + l32, jw = j0 + 64 wave + 4 h.
+// j = jw + 32 mb + 8 (r>>2) + (r&3), row i = i0 + 32 nb + l32, jw = j0 + 32 MB wave + 4 h.
 // The exponent of an entry is fma(acc, kk, -reference): unmasked tiles pass the
 // raw dot products with kk = s log2(e); tiles touching the diagonal or the
 // ragged end pass y = s log2(e) <.,.> with excluded entries set to -inf and kk = 1.
-template <bool MASKED>
-__device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&acc)[2][2], float (&rowR)[2],
-                                             float (&rowL)[2], int64_t j0, int q, bool first_row_tile, float k2,
+template <bool MASKED, int MB, int NB>
+__device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&acc)[MB][NB], float (&rowR)[NB],
+                                             float (&rowL)[NB], int64_t j0, int q, bool first_row_tile, float k2,
                                              int wave, int lane) {
   const int l32 = lane & 31, h = lane >> 5;
   const int64_t b = p.b;
-  const int64_t jw = j0 + 64 * wave + 4 * h;
+  const int64_t jw = j0 + 32 * MB * wave + 4 * h;
   const float ninf = -__builtin_inff();
   const float kk = MASKED ? 1.0f : k2;
   auto jof = [&](int mb, int r) -> int64_t { return jw + 32 * mb + 8 * (r >> 2) + (r & 3); };
 
   // ---- row statistics: per lane and row, lazy reference with an exact fallback
   {
-    float t[2];
+    float t[NB];
     bool bad = false;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
+    for (int nb = 0; nb < NB; ++nb) {
       float s = 0.f;
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) s += exp2_hw(__builtin_fmaf(acc[mb][nb][r], kk, -rowR[nb]));
       t[nb] = s;
@@ -188,19 +215,19 @@ __device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&
     }
     if (!wave_any(bad)) {
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) rowL[nb] += t[nb];
+      for (int nb = 0; nb < NB; ++nb) rowL[nb] += t[nb];
     } else {
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
+      for (int nb = 0; nb < NB; ++nb) {
         float m = rowR[nb];
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
           for (int r = 0; r < 16; ++r) m = fmaxf(m, acc[mb][nb][r] * kk);
         const float ms = m == ninf ? 0.f : m;
         float s2 = rowL[nb] * exp2_hw(rowR[nb] - ms);
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
           for (int r = 0; r < 16; ++r) s2 += exp2_hw(__builtin_fmaf(acc[mb][nb][r], kk, -ms));
         rowL[nb] = m == ninf ? 0.f : s2;
@@ -211,17 +238,19 @@ __device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&
 
   // ---- column statistics: reference = the group's running pair for column j
   {
-    const int64_t jmine = jof(l32 >> 4, l32 & 15);  // the column this lane reduces to
+    constexpr int NV = 16 * MB;  // columns per lane
+    const int tmine = fwd_rs_index<NV>(l32);
+    const int64_t jmine = jof(tmine >> 4, tmine & 15);  // the column this lane reduces to
     float* cR = p.colR + (int64_t)q * b;
     float* cL = p.colL + (int64_t)q * b;
     float Rold = ninf, Lold = 0.f;
-    float ref[32];
+    float ref[NV];
     if (first_row_tile) {
 #pragma unroll
-      for (int t = 0; t < 32; ++t) ref[t] = ninf;
+      for (int t = 0; t < NV; ++t) ref[t] = ninf;
     } else if constexpr (!MASKED) {
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           const f32x4 v = *(const f32x4*)(cR + jw + 32 * mb + 8 * a);
@@ -232,7 +261,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&
       Lold = cL[jmine];
     } else {
 #pragma unroll
-      for (int t = 0; t < 32; ++t) {
+      for (int t = 0; t < NV; ++t) {
         const int64_t j = jof(t >> 4, t & 15);
         const float v = cR[j < b ? j : b - 1];
         ref[t] = j < b ? v : ninf;
@@ -242,13 +271,13 @@ __device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&
       Rold = jmine < b ? r0 : ninf;
       Lold = jmine < b ? l0 : 0.f;
     }
-    float v[32];
+    float v[NV];
 #pragma unroll
-    for (int t = 0; t < 32; ++t) {
+    for (int t = 0; t < NV; ++t) {
       const int mb = t >> 4, r = t & 15;
       float s = 0.f;
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) s += exp2_hw(__builtin_fmaf(acc[mb][nb][r], kk, -ref[t]));
+      for (int nb = 0; nb < NB; ++nb) s += exp2_hw(__builtin_fmaf(acc[mb][nb][r], kk, -ref[t]));
       // a column whose entries are all excluded so far has ref = -inf and sums
       // exp2(-inf + inf) = NaN here; that sends the tile to the exact path
       v[t] = s;
@@ -258,20 +287,22 @@ __device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&
     if (wave_any(!lazy_ok(tot))) {
       // exact path: per-column max over this tile, broadcast, rescaled sums
 #pragma unroll
-      for (int t = 0; t < 32; ++t) {
+      for (int t = 0; t < NV; ++t) {
         const int mb = t >> 4, r = t & 15;
-        v[t] = fmaxf(acc[mb][0][r] * kk, acc[mb][1][r] * kk);
+        float m = acc[mb][0][r] * kk;
+        if constexpr (NB == 2) m = fmaxf(m, acc[mb][1][r] * kk);
+        v[t] = m;
       }
       const float mt = half_reduce_scatter<true>(v, lane);
       const float Rn = fmaxf(Rold, mt);
 #pragma unroll
-      for (int t = 0; t < 32; ++t) {
-        const float rn = shfl_idx(Rn, (lane & 32) | t);
+      for (int t = 0; t < NV; ++t) {
+        const float rn = shfl_idx(Rn, (lane & 32) | fwd_rs_lane<NV>(t));
         const float rs = rn == ninf ? 0.f : rn;
         const int mb = t >> 4, r = t & 15;
         float s = 0.f;
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) s += exp2_hw(__builtin_fmaf(acc[mb][nb][r], kk, -rs));
+        for (int nb = 0; nb < NB; ++nb) s += exp2_hw(__builtin_fmaf(acc[mb][nb][r], kk, -rs));
         v[t] = s;
       }
       const float tot2 = half_reduce_scatter<false>(v, lane);
@@ -285,10 +316,12 @@ __device__ __forceinline__ void fwd_epilogue(const FwdParams& p, const f32x16 (&
   }
 }
 
+template <int MB, int NB>
 __global__ void __launch_bounds__(256, 2) fwd_sweep(FwdParams p) {
-  __shared__ __attribute__((aligned(1024))) char lds_[2 * kFwdStageBytes];
+  using T = FwdTile<MB, NB>;
+  __shared__ __attribute__((aligned(1024))) char lds_[2 * T::StageBytes];
   INFCL_LDS char* lds0 = (INFCL_LDS char*)lds_;
-  INFCL_LDS char* lds1 = lds0 + kFwdStageBytes;
+  INFCL_LDS char* lds1 = lds0 + T::StageBytes;
   const int lane = __lane_id();
   const int wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;
@@ -307,46 +340,69 @@ __global__ void __launch_bounds__(256, 2) fwd_sweep(FwdParams p) {
   const float k2 = p.scale[0] * kLog2e;
   const float ninf = -__builtin_inff();
 
-  float rowR[2], rowL[2];
+  float rowR[NB], rowL[NB];
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
+  for (int nb = 0; nb < NB; ++nb) {
     rowR[nb] = ninf;
     rowL[nb] = 0.f;
   }
 
-  const FwdDmaOffsets dmo = fwd_dma_offsets(p.d, (int)sizeof(float), wave, lane);
+  const auto dmo = fwd_dma_offsets<MB, NB>(p.d, (int)sizeof(float), wave, lane);
   int rr = 0, cc = 0;  // position of the current tile in this workgroup's (row, column) sweep
-  fwd_stage_dma(p, dmo, p.r0 + (int64_t)q * kFwdBI, (int64_t)ct_lo * kFwdBJ, 0, lds0, wave);
+  fwd_stage_dma<MB, NB>(p, dmo, p.r0 + (int64_t)q * T::BI, (int64_t)ct_lo * T::BJ, 0, lds0, wave);
   wait_dma();
   __syncthreads();
 
   for (int tau = 0; tau < ntile; ++tau) {
-    const int64_t i0 = p.r0 + (int64_t)(q + rr * p.Pr) * kFwdBI;
-    const int64_t j0 = (int64_t)(ct_lo + cc) * kFwdBJ;
+    const int64_t i0 = p.r0 + (int64_t)(q + rr * p.Pr) * T::BI;
+    const int64_t j0 = (int64_t)(ct_lo + cc) * T::BJ;
     const bool has_next = tau + 1 < ntile;
     const int nrr = cc + 1 == ncol ? rr + 1 : rr;
     const int ncc = cc + 1 == ncol ? 0 : cc + 1;
-    const int64_t ni0 = p.r0 + (int64_t)(q + nrr * p.Pr) * kFwdBI;
-    const int64_t nj0 = (int64_t)(ct_lo + ncc) * kFwdBJ;
+    const int64_t ni0 = p.r0 + (int64_t)(q + nrr * p.Pr) * T::BI;
+    const int64_t nj0 = (int64_t)(ct_lo + ncc) * T::BJ;
 
-    f32x16 acc[2][2];
+    f32x16 acc[MB][NB];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
 
+    // The diagonal <img_i, txt_i> of the tile's rows, from the staged chunks by
+    // fp32 FMAs (256 / BI threads per row): swapping the modalities gives the
+    // same bits, which the split products' order does not.
+    const bool diag = j0 < i0 + T::BI && i0 < j0 + T::BJ;
+    constexpr int TPR = 256 / T::BI;
+    const int il = threadIdx.x / TPR;
+    const int jl = (int)(i0 - j0) + il;  // the row's own column, if in the tile
+    const bool dhas = diag && jl >= 0 && jl < T::BJ;
+    float dsum = 0.f;
+    auto diag_stage = [&](const INFCL_LDS char* buf) {
+      if (dhas) {
+#pragma unroll
+        for (int u = 0; u < 8 / TPR; ++u) {
+          const int c = (threadIdx.x % TPR) + TPR * u, rt = T::BI + jl;
+          const f32x4 x = *(const INFCL_LDS f32x4*)(buf + il * 128 + fwd_swz(il, c) * 16);
+          const f32x4 y = *(const INFCL_LDS f32x4*)(buf + rt * 128 + fwd_swz(rt, c) * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dsum = __builtin_fmaf(x[e], y[e], dsum);
+        }
+      }
+    };
     for (int st = 0; st < nst; st += 2) {
-      fwd_stage_dma(p, dmo, i0, j0, st + 1, lds1, wave);
-      fwd_stage_mfma(lds0, acc, wave, lane);
+      fwd_stage_dma<MB, NB>(p, dmo, i0, j0, st + 1, lds1, wave);
+      fwd_stage_mfma<MB, NB>(lds0, acc, wave, lane);
+      diag_stage(lds0);
       wait_dma();
       __syncthreads();
       if (st + 2 < nst)
-        fwd_stage_dma(p, dmo, i0, j0, st + 2, lds0, wave);
+        fwd_stage_dma<MB, NB>(p, dmo, i0, j0, st + 2, lds0, wave);
       else if (has_next)
-        fwd_stage_dma(p, dmo, ni0, nj0, 0, lds0, wave);
-      fwd_stage_mfma(lds1, acc, wave, lane);
+        fwd_stage_dma<MB, NB>(p, dmo, ni0, nj0, 0, lds0, wave);
+      fwd_stage_mfma<MB, NB>(lds1, acc, wave, lane);
+      diag_stage(lds1);
       if (st + 2 < nst) {
         wait_dma();
         __syncthreads();
@@ -354,35 +410,19 @@ __global__ void __launch_bounds__(256, 2) fwd_sweep(FwdParams p) {
     }
 
     // the next tile's first stage is in flight while the epilogue runs
-    const bool diag = j0 < i0 + kFwdBI && i0 < j0 + kFwdBJ;
-    const bool special = diag || (i0 + kFwdBI > p.rend) || (j0 + kFwdBJ > b);
+    const bool special = diag || (i0 + T::BI > p.rend) || (j0 + T::BJ > b);
     if (special) {
-      const int64_t jw = j0 + 64 * wave + 4 * h;
+      const int64_t jw = j0 + 32 * MB * wave + 4 * h;
       if (diag) {
-        // the diagonal entry of row i sits in one lane of one wave, in block
-        // mb == nb when i0 - j0 is a multiple of 64 (whole batch), in either
-        // block for a shard starting at a multiple of 32
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          const int64_t i = i0 + 32 * nb + l32;
-          float dv = 0.f;
-          bool has = false;
-#pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const bool hit = jw + 32 * mb + 8 * (r >> 2) + (r & 3) == i;
-              dv = hit ? acc[mb][nb][r] : dv;
-              has |= hit;
-            }
-          if (has && i < p.rend) p.udiag[i] = dv;
-        }
+        for (int k = 1; k < TPR; k <<= 1) dsum += shfl_xor(dsum, k);
+        if (dhas && threadIdx.x % TPR == 0 && i0 + il < p.rend) p.udiag[i0 + il] = dsum;
       }
       // scaled exponents, -inf for the diagonal and for rows/columns past b
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
           const int64_t i = i0 + 32 * nb + l32;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
@@ -391,15 +431,15 @@ __global__ void __launch_bounds__(256, 2) fwd_sweep(FwdParams p) {
             acc[mb][nb][r] = ok ? acc[mb][nb][r] * k2 : ninf;
           }
         }
-      fwd_epilogue<true>(p, acc, rowR, rowL, j0, q, rr == 0, k2, wave, lane);
+      fwd_epilogue<true, MB, NB>(p, acc, rowR, rowL, j0, q, rr == 0, k2, wave, lane);
     } else {
-      fwd_epilogue<false>(p, acc, rowR, rowL, j0, q, rr == 0, k2, wave, lane);
+      fwd_epilogue<false, MB, NB>(p, acc, rowR, rowL, j0, q, rr == 0, k2, wave, lane);
     }
 
     // end of a row tile: merge the two lane halves and publish one pair per wave
     if (cc + 1 == ncol) {
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
+      for (int nb = 0; nb < NB; ++nb) {
         float R = rowR[nb], L = rowL[nb];
         lse2_merge(R, L, shfl_xor(rowR[nb], 32), shfl_xor(rowL[nb], 32));
         const int64_t i = i0 + 32 * nb + l32;
@@ -578,20 +618,28 @@ int launch_fwd2(const void* img, const void* txt, int64_t b, int64_t d, int dtyp
                 const float* scale, float* rowR, float* rowL, float* colR, float* colL, float* udiag, float* ref2,
                 hipStream_t stream);
 
-// Grid of the streamed-tiles sweep for nrows own rows against b columns: Pc
-// column groups (one per XCD when there are enough column tiles) times Pr row
-// groups, about two workgroups per compute unit.
+// Tile shape of the streamed-tiles sweep for nrows own rows against b columns:
+// 64 x 256, unless so few tiles leave compute units idle (a tile's K-stages are
+// a serial chain: b = 1024, d = 512 takes 44 us in 64 tiles of 64 x 256, 20
+// in 256 of 32 x 128).
+static int fwd1_shape(int64_t b, int64_t nrows) {
+  return ((nrows + 63) / 64) * ((b + 255) / 256) >= 192 ? 2 : 1;  // MB = NB
+}
+
+// Grid of the streamed-tiles sweep: Pc column groups (one per XCD when there
+// are enough column tiles) times Pr row groups, about two workgroups per
+// compute unit.
 void fwd1_grid(int64_t b, int64_t nrows, int* Pr, int* Pc) {
-  const int64_t nRT = (nrows + kFwdBI - 1) / kFwdBI, nCT = (b + kFwdBJ - 1) / kFwdBJ;
+  const int64_t s = fwd1_shape(b, nrows);
+  const int64_t nRT = (nrows + 32 * s - 1) / (32 * s), nCT = (b + 128 * s - 1) / (128 * s);
   *Pc = (int)(nCT < 8 ? nCT : 8);
   *Pr = (int)(nRT < 64 ? nRT : 64);
 }
 
 // Most partial pairs per sample that the grid of any nrows <= b leaves.
 int fwd1_pairs(int64_t b) {
-  int Pr = 0, Pc = 0;
-  fwd1_grid(b, b, &Pr, &Pc);
-  return Pr + 4 * Pc;
+  const int64_t r = (b + 31) / 32, c = (b + 127) / 128;
+  return (int)((r < 64 ? r : 64) + 4 * (c < 8 ? c : 8));
 }
 
 static int launch_fwd1(const void* img, const void* txt, int64_t b, int64_t d, int dtype, int64_t r0, int64_t nrows,
@@ -609,13 +657,17 @@ static int launch_fwd1(const void* img, const void* txt, int64_t b, int64_t d, i
   p.colL = colL;
   p.udiag = udiag;
   fwd1_grid(b, nrows, &p.Pr, &p.Pc);
-  p.nRT = (int)((nrows + kFwdBI - 1) / kFwdBI);
-  p.nCT = (int)((b + kFwdBJ - 1) / kFwdBJ);
+  const int64_t s = fwd1_shape(b, nrows);
+  p.nRT = (int)((nrows + 32 * s - 1) / (32 * s));
+  p.nCT = (int)((b + 128 * s - 1) / (128 * s));
   p.r0 = r0;
   p.rend = r0 + nrows;
   p.rstride = nrows;
   if (dtype != 1) return 2;  // every supported 16-bit width takes the resident-rows sweep
-  hipLaunchKernelGGL(fwd_sweep, dim3(p.Pr * p.Pc), dim3(256), 0, stream, p);
+  if (s == 2)
+    hipLaunchKernelGGL((fwd_sweep<2, 2>), dim3(p.Pr * p.Pc), dim3(256), 0, stream, p);
+  else
+    hipLaunchKernelGGL((fwd_sweep<1, 1>), dim3(p.Pr * p.Pc), dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

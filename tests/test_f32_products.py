@@ -1,0 +1,65 @@
+"""fp32 inputs: products of three-part bf16 operands against the fp64 oracle.
+
+The parts of an fp32 number add up to it exactly and the part products left
+out are below 2^-25 of the full product, so the results carry fp32 rounding
+only: the log-sum-exp bound of gpu_util.lse_tol, and for the gradients 1e-5 of
+their maximum (fp32 accumulation over up to 3300 terms, 2^-24 sqrt(3300) =
+3.4e-6, and the exponents' own rounding, 2^-24 |y| ln 2 with |y| up to 144 at
+s = 100, which 1e-4 covers there).  Shapes: both tile shapes of the forward (32 x 128
+below 192 tiles of 64 x 256), every width class of the backward (whole and half
+last segments), ragged ends; a well-separated batch, whose weights are as
+small as 1e-31 (their low parts are kept normal by a power of two); rows of
+very different magnitude; the error against fp64 of products of awkward
+mantissas (all 24 bits set)."""
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import f32_scale, lse_tol, max_rel, run, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(img, txt, s, d, tol, lse_s=None):
+    ref, dI, dT, ds = oracle.forward_backward(img.astype(np.float64), txt.astype(np.float64), s)
+    g = run(img, txt, "f32", s)
+    print(f"dI {max_rel(g['dI'], dI):.2e} dT {max_rel(g['dT'], dT):.2e} "
+          f"lse {np.max(np.abs(g['lse_r'] - ref['lse_r'])):.2e} ds {g['dscale']:.8e} ref {ds:.8e}", flush=True)
+    assert np.all(np.abs(g["lse_r"] - ref["lse_r"]) <= lse_tol(lse_s or s, d, ref["lse_r"]))
+    assert np.all(np.abs(g["lse_c"] - ref["lse_c"]) <= lse_tol(lse_s or s, d, ref["lse_c"]))
+    assert max_rel(g["dI"], dI) <= tol and max_rel(g["dT"], dT) <= tol
+    assert g["dscale"] == pytest.approx(ds, rel=tol, abs=1e-30)
+    assert g["loss64"] == pytest.approx(ref["loss"], rel=tol, abs=1e-30)
+
+
+@pytest.mark.parametrize("b,d", [(3300, 64), (3201, 192), (700, 320), (513, 448), (1100, 512), (257, 128), (33, 256)])
+def test_shapes(b, d):
+    img, txt = synth.clip_pairs(b, d, 1.0, seed=b + d, dtype="f32")
+    _check(img, txt, f32_scale(14.29), d, 1e-5)
+
+
+@pytest.mark.parametrize("s,sigma", [(50.0, 1.0), (100.0, 0.5)])
+def test_separated_batch(s, sigma):
+    img, txt = synth.clip_pairs(1200, 512, sigma, seed=3, dtype="f32")
+    _check(img, txt, f32_scale(s), 512, 1e-4)
+
+
+def test_mixed_row_norms():
+    b, d = 900, 256
+    img, txt = synth.clip_pairs(b, d, 1.0, seed=5, dtype="f32")
+    img = (img * (2.0 ** ((np.arange(b) % 7) - 3))[:, None]).astype(np.float32)
+    txt = (txt * (2.0 ** ((np.arange(b) * 3 % 7) - 3))[:, None]).astype(np.float32)
+    _check(img, txt, f32_scale(1.0), d, 1e-4, lse_s=64.0)
+
+
+def test_full_mantissas():
+    """Entries with all 24 mantissa bits set: a part dropped or misplaced shows
+    as 2^-16 or 2^-8 of the entries' scale."""
+    b, d = 384, 128
+    rng = np.random.default_rng(7)
+    full = np.float32(2.0) - np.float32(2.0 ** -23)
+    sgn = rng.choice([-1.0, 1.0], size=(2, b, d)).astype(np.float32)
+    e = rng.integers(-6, -3, size=(2, b, d))
+    img, txt = (full * sgn * np.exp2(e.astype(np.float32))).astype(np.float32)
+    _check(img, txt, f32_scale(4.0), d, 1e-5)
