@@ -249,13 +249,13 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
   // VALU cycles between the tile's phases): the DMA source offset of this
   // lane, the column-pair slot offset, and GEMM1's swept fragment offsets
   // (tile base + kSeg (n >> 3) + offA[n & 7]).
-  const uint32_t dma_lo = sweep_dma_lane_off(lane, wq, ROWG);
-  // d > 512 (registers to spare): the full source offset of each of the
-  // wave's DMA instructions, computed once, so that no VALU instruction
-  // writes a DMA operand inside the sweep and the DMA needs one wait state
-  uint32_t dvo[D > 512 ? NIW : 1];
-#pragma unroll
-  for (int k = 0; k < (D > 512 ? NIW : 1); ++k) dvo[k] = dma_lo + sweep_dma_kk_off(kk0 + k, wq, ROWG);
+  // The DMA offset of instruction kk0 + k: the wave's part (its 4 rows, and its
+  // half of the tile's instructions where that is an even number), kept in the
+  // lane part, plus a compile-time constant, the scalar operand; with an odd
+  // share (d = 128, 384) the two halves differ in the constant too.
+  constexpr bool kEven = NW == 4 || NIW % 2 == 0;
+  const uint32_t dma_lo = sweep_dma_lane_off(lane, wq, ROWG) + 4 * wq * ROWG + (kEven ? sweep_dma_kk_off(kk0, 0, ROWG) : 0);
+  auto kk_const = [&](int k) { return sweep_dma_kk_off(kEven ? k : kk0 + k, 0, ROWG); };
   const uint32_t slot_lo = 16u * (uint32_t)(lane & 7);
   int offA[8];
   {
@@ -266,17 +266,16 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
   // swept row (tile-relative) of accumulator entry r of this lane
   auto jrow = [&](int r) { return 16 * (r >> 3) + 8 * h + (r & 7); };
   auto tile_rsrc = [&](int jt) {
-    const int j0 = (jt < 0 ? 0 : jt) * kSweepBN;
-    return rsrc_words((const char*)p.txt + (int64_t)j0 * ROWG, jt < 0 ? 0 : (int64_t)(b - j0) * ROWG);
+    return sweep_tile_rsrc((const char*)p.txt + (int64_t)jt * TILEB, jt < ct_hi ? b - jt * kSweepBN : 0, ROWG);
   };
   // running column pairs of tile jt into slot: on a workgroup's first row
   // block the reference is the diagonal value and the sum empty (a resource
   // of zero bytes loads zeros)
   auto issue_slot = [&](int jt, bool first_rb, INFCL_LDS float* slot) {
-    const int j0 = (jt < 0 ? 0 : jt) * kSweepBN;
-    const int64_t nb = jt < 0 ? 0 : (int64_t)(b - j0) * 4;
-    dma16_asm(rsrc_words(first_rb ? p.ref2 + j0 : cR + j0, nb), slot, slot_lo);
-    dma16_asm(rsrc_words(cL + j0, first_rb ? 0 : nb), slot + 256, slot_lo);
+    const int j0 = jt * kSweepBN;
+    const int rem = jt < ct_hi ? b - j0 : 0;
+    dma16_asm(sweep_tile_rsrc((first_rb ? p.ref2 : cR) + j0, rem, 4), slot, slot_lo);
+    dma16_asm(sweep_tile_rsrc(cL + j0, first_rb ? 0 : rem, 4), slot + 256, slot_lo);
   };
 
   for (int rb = q; rb < p.nRB; rb += p.Pr) {
@@ -312,7 +311,7 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
       const u32x4 rs = tile_rsrc(ct_lo);
 #pragma unroll
       for (int k = 0; k < NIW; ++k)
-        dma16_asm(rs, tA + 1024 * (wq + 4 * (kk0 + k)), dma_lo + sweep_dma_kk_off(kk0 + k, wq, ROWG));
+        dma16_asm(rs, tA + 1024 * (wq + 4 * (kk0 + k)), dma_lo, kk_const(k));
       if (slot_wave) issue_slot(ct_lo, first_rb, sA);
     }
     wait_dma();
@@ -394,11 +393,12 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
           mfma16_vgpr<F16, false>(sacc, ring[s2 % kPre], ownf[s2], s2 == 0, s2 == KS - 1);
         constexpr int SPI = KS / NIW;  // steps per DMA instruction
         if ((s2 + 1) % SPI == 0) {
-          const int kk = kk0 + (s2 + 1) / SPI - 1;
+          constexpr int k = (s2 + 1) / SPI - 1;
+          // d > 512 (registers to spare): one wait state
           if constexpr (D > 512)
-            dma16_asm_w1(drs, nxt + 1024 * (wq + 4 * kk), dvo[(s2 + 1) / SPI - 1]);
+            dma16_asm_w1(drs, nxt + 1024 * (wq + 4 * (kk0 + k)), dma_lo, kk_const(k));
           else
-            dma16_asm(drs, nxt + 1024 * (wq + 4 * kk), dma_lo + sweep_dma_kk_off(kk, wq, ROWG));
+            dma16_asm(drs, nxt + 1024 * (wq + 4 * (kk0 + k)), dma_lo, kk_const(k));
         }
         if (slot_wave && s2 == (KS > 1 ? 1 : 0)) issue_slot(jn, first_rb, snxt);
         if constexpr (s2 + kPre < KS) {
@@ -518,7 +518,7 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
     // partial pairs into LDS
     auto body = [&](int jt, const INFCL_LDS char* cur, const INFCL_LDS float* scur, INFCL_LDS char* nxt,
                     INFCL_LDS float* snxt, int par) {
-      const int jn = jt + 1 < ct_hi ? jt + 1 : -1;
+      const int jn = jt + 1;  // past the group's end: resources of zero bytes
       const float Rmine = scur[jl_lane], Lmine = scur[256 + jl_lane];
       const float Rold = scur[jc], Lold = scur[256 + jc];
       float prw[NW], psw[NW];
