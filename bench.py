@@ -298,9 +298,9 @@ def main():
 
     entries = float(b) * float(b)
     value = entries / (ms_per_step * 1e-3)
-    bwd_launch_ms = sum(bwd_ms) / len(bwd_ms) / 2.0   # two sweep launches per infcl_bwd call
+    bwd_launch_ms = sum(bwd_ms) / len(bwd_ms) / 2.0   # one side of the two that an infcl_bwd call sweeps
     # 16-bit inputs with d = 768 or 1024 run the single-pass wide-row sweep
-    bwd_kernel = "bwd_wide" if dt_name != "f32" and d in (768, 1024) else "bwd_sweep"
+    bwd_kernel = "bwd_f32" if dt_name == "f32" else "bwd_wide" if d >= 640 else "bwd_sweep"
     fwd_launch_ms = sum(fwd_ms) / len(fwd_ms)
     peak = FP32_MFMA_PEAK if dt_name == "f32" else BF16_PEAK  # fp16 and bf16 dense MFMA peaks are equal
     alg_bwd_launch = 3.0 * entries * d      # half of the 6 b^2 d algorithmic backward flops
@@ -344,7 +344,7 @@ def main():
         "step_ms_min": min(step_ms),
         "peak_hbm_bytes": int(peak_bytes - base_mem + (img.numel() + txt.numel()) * img.element_size()),
         "roofline": {
-            "kernel": f"{bwd_kernel} (one of the two backward launches)",
+            "kernel": f"{bwd_kernel} (one side: half of the backward launch)",
             "bound": "mfma" if intensity >= ridge else "hbm",
             "intensity_flop_per_byte": intensity,
             "ridge_flop_per_byte": ridge,

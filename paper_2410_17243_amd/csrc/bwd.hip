@@ -392,8 +392,10 @@ __global__ void __launch_bounds__(256, 1) bwd_sweep(BwdParams p) {
         wait_dma();
         __syncthreads();
       };
-      // Unrolled over the buffer rotation without tests in between: a tile
-      // index past the end is a tile of rows past the end, fully masked (zero G').
+      // Unrolled over the buffer rotation without tests in between (with them
+      // the accumulators spill): a tile index past the end is a tile of rows past
+      // the end, fully masked (zero G').  Parts of a split block are multiples of
+      // three tiles (BwdPlan::gran).
       for (int jt = 0; jt < ntile; jt += 3) {
         body(jt, tA, tB, lB, tC, lC);
         body(jt + 1, tB, tC, lC, tA, lA);
@@ -581,6 +583,8 @@ BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
   pl.nblk = (int)((nrows + pl.bm - 1) / pl.bm);
   const int total = 2 * pl.nblk;
   const int64_t ntile = (b + kBwdBN - 1) / kBwdBN;
+  pl.gran = dtype != 1 && pl.bm == kBwdBM ? 3 : 1;
+  const int64_t nunit = (ntile + pl.gran - 1) / pl.gran;
   pl.nfull = total / kCUs * kCUs;
   pl.ns = 1;
   pl.part_bytes = 0;
@@ -590,12 +594,12 @@ BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
     const double t_tile = (dtype == 1 ? 0.011 : 3.7e-3) * (double)d;
     const double blk_bytes = (double)pl.bm * (double)d * 4.0;
     double best = 0.0;
-    for (int ns = 1; ns <= 64 && ns <= ntile; ++ns) {
+    for (int ns = 1; ns <= 64 && ns <= nunit; ++ns) {
       const int64_t parts = (int64_t)rem * ns;
       const double bytes = (double)parts * blk_bytes;
       if (ns > 1 && bytes + 8.0 * (double)(pl.nfull + parts) > (double)cap) break;
       const double rounds = (double)((parts + kCUs - 1) / kCUs);
-      double t = rounds * (8.0 + t_tile * (double)((ntile + ns - 1) / ns));
+      double t = rounds * (8.0 + t_tile * (double)((nunit + ns - 1) / ns * pl.gran));
       if (ns > 1) t += 6.0 + bytes / 2.0e6;
       if (ns == 1 || t < best) {
         best = t;
@@ -646,6 +650,7 @@ int launch_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype
   p.nblk = pl.nblk;
   p.nfull = pl.nfull;
   p.ns = pl.ns;
+  p.gran = pl.gran;
   p.part = part;
   const int64_t split = 2 * (int64_t)pl.nblk - pl.nfull;  // split row blocks
   p.ds_part = pl.ns > 1 ? (double*)(part + split * pl.ns * pl.bm * d) : ds_part;

@@ -31,9 +31,9 @@ struct BwdParams {
   int gdt;                   // gradient type, which chooses the kernel instantiation: 0 fp32, 1 16-bit
   // Work split (plan_bwd): of the 2 nblk row blocks (image side first) the
   // first nfull are swept whole, one workgroup each; each of the others is
-  // swept by ns workgroups, a contiguous range of tiles each, whose unscaled
+  // swept by ns workgroups, a contiguous range of whole groups of gran tiles each, whose unscaled
   // fp32 sums go to part[(block - nfull) ns + k][rows][d] for bwd_reduce.
-  int nblk, nfull, ns;
+  int nblk, nfull, ns, gran;
   float* part;
 };
 
@@ -59,11 +59,12 @@ __device__ __forceinline__ BwdTask bwd_task(const BwdParams& p, int bm_d) {
     const uint32_t r = wg - p.nfull, ns = p.ns;
     const uint32_t q = __builtin_amdgcn_readfirstlane(r / ns), k = r - q * ns;
     blk = p.nfull + (int)q;
-    // ntile k < 2^31: ntile <= 2^25, k < ns <= 64
-    const int t0 = (int)__builtin_amdgcn_readfirstlane(ntile * k / ns);
-    const int t1 = (int)__builtin_amdgcn_readfirstlane(ntile * (k + 1) / ns);
-    t.row0 = t0 * kBwdBN;
-    t.rows = (t1 == (int)ntile ? (int)p.b : t1 * kBwdBN) - t.row0;
+    const uint32_t g = p.gran, nunit = (ntile + g - 1) / g;
+    // nunit (k + 1) <= 2^31: ntile <= 2^25, k < ns <= 64
+    const uint32_t t0 = __builtin_amdgcn_readfirstlane(nunit * k / ns * g);
+    const uint32_t t1 = __builtin_amdgcn_readfirstlane(nunit * (k + 1) / ns * g);
+    t.row0 = (int)t0 * kBwdBN;
+    t.rows = (t1 >= ntile ? (int)p.b : (int)t1 * kBwdBN) - t.row0;
     t.part = p.part + (int64_t)r * bm_d;
   }
   t.sd = blk >= p.nblk ? 1 : 0;
@@ -76,6 +77,7 @@ struct BwdPlan {
   int bm;           // own rows per row block
   int nblk;         // row blocks per side
   int nfull, ns;    // blocks swept whole; parts of each other block
+  int gran;         // tiles that a part's range is a multiple of (what the sweep's loop unrolls)
   int nwg;          // workgroups
   size_t part_bytes;  // partial sums and dscale partials (0 when nothing is split)
 };

@@ -493,13 +493,14 @@ struct FinParams {
 // (25 against 17 us at b = 131072, where it is 1e-4 of the forward).
 constexpr int kFinT = 32, kFinG = 8;
 
-// natural-log log-sum-exp of the n base-2 partial pairs (R, l) of sample t at
-// R/L[k stride + t], in every thread of the sample; an empty pair (R = -inf)
-// weighs zero.  Each thread keeps up to eight pairs in registers.  The order of
-// the additions is fixed by n alone.
-__device__ __forceinline__ double merge_parts(const float* R, const float* L, int n, int64_t stride, int64_t t, bool ok,
-                                              int tl, int g, float (*sm)[kFinT], double (*ss)[kFinT]) {
-  float M = -__builtin_inff();
+// Level M and sum S (log2 S + M the merged value) of the n base-2 partial pairs
+// (R, l) of sample t at R/L[k stride + t], in every thread of the sample; an
+// empty pair (R = -inf) weighs zero.  Each thread keeps up to eight pairs in
+// registers.  The order of the additions is fixed by n alone.
+__device__ __forceinline__ void merge_parts(const float* R, const float* L, int n, int64_t stride, int64_t t, bool ok,
+                                            int tl, int g, float (*sm)[kFinT], double (*ss)[kFinT], float& M,
+                                            double& S) {
+  M = -__builtin_inff();
   float r[8], l[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
@@ -515,7 +516,7 @@ __device__ __forceinline__ double merge_parts(const float* R, const float* L, in
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kFinG; ++k) M = fmaxf(M, sm[k][tl]);
-  double S = 0.0;
+  S = 0.0;
   if (M != -__builtin_inff()) {
 #pragma unroll
     for (int u = 0; u < 8; ++u)
@@ -531,7 +532,9 @@ __device__ __forceinline__ double merge_parts(const float* R, const float* L, in
   S = 0.0;
 #pragma unroll
   for (int k = 0; k < kFinG; ++k) S += ss[k][tl];
-  // natural-log LSE over the off-diagonal entries
+}
+// ... as a natural-log log-sum-exp over the off-diagonal entries
+__device__ __forceinline__ double merged_lse(float M, double S) {
   return M == -__builtin_inff() ? -__builtin_inf() : ((double)M + log2(S)) * 0.6931471805599453;
 }
 
@@ -546,9 +549,12 @@ __global__ void __launch_bounds__(256) fwd_finalize(FinParams p) {
   const int tl = threadIdx.x & (kFinT - 1), g = threadIdx.x / kFinT;
   const int64_t t = (int64_t)blockIdx.x * kFinT + tl;
   const bool ok = t < p.n;
-  const double offr = merge_parts(p.rowR, p.rowL, p.nrowpart, p.rstride, t, ok, tl, g, smr, ssr);
-  const double offc = merge_parts(p.colR, p.colL, p.ncolpart, p.cstride, t, ok, tl, g, smc, ssc);
+  float Mr, Mc;
+  double Sr, Sc;
+  merge_parts(p.rowR, p.rowL, p.nrowpart, p.rstride, t, ok, tl, g, smr, ssr, Mr, Sr);
+  merge_parts(p.colR, p.colL, p.ncolpart, p.cstride, t, ok, tl, g, smc, ssc, Mc, Sc);
   if (g == 0) {
+    const double offr = merged_lse(Mr, Sr), offc = merged_lse(Mc, Sc);
     double contrib = 0.0;
     if (ok) {
       const double u = (double)p.udiag[p.r0 + t];
@@ -578,18 +584,17 @@ __global__ void __launch_bounds__(256) fwd_finalize(FinParams p) {
 // receives from every shard.
 __global__ void __launch_bounds__(256) fwd_col_pairs(const float* colR, const float* colL, int ncolpart, int64_t b,
                                                      float* out) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= b) return;
-  float M = -__builtin_inff();
-  for (int k = 0; k < ncolpart; ++k) M = fmaxf(M, colR[(int64_t)k * b + j]);
-  double S = 0.0;
-  if (M != -__builtin_inff())
-    for (int k = 0; k < ncolpart; ++k) {
-      const float r = colR[(int64_t)k * b + j];
-      if (r != -__builtin_inff()) S += (double)colL[(int64_t)k * b + j] * exp2((double)r - (double)M);
-    }
-  out[j] = M;
-  out[b + j] = (float)S;
+  __shared__ float sm[kFinG][kFinT];
+  __shared__ double ss[kFinG][kFinT];
+  const int tl = threadIdx.x & (kFinT - 1), g = threadIdx.x / kFinT;
+  const int64_t j = (int64_t)blockIdx.x * kFinT + tl;
+  float M;
+  double S;
+  merge_parts(colR, colL, ncolpart, b, j, j < b, tl, g, sm, ss, M, S);
+  if (g == 0 && j < b) {
+    out[j] = M;
+    out[b + j] = (float)S;
+  }
 }
 
 // Fixed-order sum of `n` fp64 partials, times `mul`; one workgroup.
@@ -763,7 +768,7 @@ int launch_fwd_shard(const void* img, const void* txt, int64_t b, int64_t d, int
   const int rc =
       launch_sweep(img, txt, b, d, dtype, r0, nrows, scale, pairs, udiag, ref2, stream, &nrowpart, &ncolpart, &pp);
   if (rc != 0) return rc;
-  hipLaunchKernelGGL(fwd_col_pairs, dim3((unsigned)((b + 255) / 256)), dim3(256), 0, stream, (const float*)pp.colR,
+  hipLaunchKernelGGL(fwd_col_pairs, dim3((unsigned)((b + kFinT - 1) / kFinT)), dim3(256), 0, stream, (const float*)pp.colR,
                      (const float*)pp.colL, ncolpart, b, colpair);
   return hipGetLastError() == hipSuccess ? 0 : 1;
 }
