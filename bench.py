@@ -299,7 +299,7 @@ def main():
     entries = float(b) * float(b)
     value = entries / (ms_per_step * 1e-3)
     bwd_launch_ms = sum(bwd_ms) / len(bwd_ms) / 2.0   # one side of the two that an infcl_bwd call sweeps
-    # 16-bit inputs with d = 768 or 1024 run the single-pass wide-row sweep
+    # 16-bit inputs with d >= 640 run the wide-row sweeps
     bwd_kernel = "bwd_f32" if dt_name == "f32" else "bwd_wide" if d >= 640 else "bwd_sweep"
     fwd_launch_ms = sum(fwd_ms) / len(fwd_ms)
     peak = FP32_MFMA_PEAK if dt_name == "f32" else BF16_PEAK  # fp16 and bf16 dense MFMA peaks are equal
