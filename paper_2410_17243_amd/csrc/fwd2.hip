@@ -11,8 +11,12 @@
 // and sweeps the text tiles of column group g (32 rows each, streamed through
 // LDS by DMA in the swept-tile layout).  Each tile is one 32 x 32 block of S^T
 // per wave.  Only text tiles move: 32 KiB of DMA per tile and workgroup for
-// 8.4 MFLOP at d = 512 with 8 waves.  g = blockIdx mod P_c, so with P_c = 8 the
-// workgroups of a column group share one XCD and its L2.
+// 8.4 MFLOP at d = 512 with 8 waves.  Each XCD takes one contiguous range of
+// the (g, q) pairs, g outermost (xcd_slot), and so as few column groups as the
+// grid allows, whose text its L2 serves to all their workgroups.  With
+// g = blockIdx mod P_c that held only where P_c is a multiple of 8: at 28 x 9
+// every XCD streamed all text rows (fp16 forward b = 50000, d = 768 4.86 ->
+// 4.68 ms; 20 x 12 at b = 5000, d = 512, 5 MB of text, 49.9 and 49.7 us).
 //  - d <= 512: NW = 8 waves, one workgroup per CU (d/4 VGPRs of own rows).
 //  - d > 512: the own rows take d/4 registers of the wave's 512, so NW = 4
 //    (one wave per SIMD) and the own-row operand lives in AGPRs, which the
@@ -43,6 +47,7 @@
 //  unrelated LDS reads.
 #include <utility>
 
+#include "grid.hpp"
 #include "sweep.hpp"
 
 
@@ -235,8 +240,9 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
   // branch-free, by every wave (4 waves)
   const bool slot_wave = NW == 4 || wave == 0;
   const int b = (int)p.b;  // at most 2^30
-  const int g = blockIdx.x % p.Pc;
-  const int q = blockIdx.x / p.Pc;
+  const uint32_t slot = xcd_slot(blockIdx.x, (uint32_t)(p.Pr * p.Pc));
+  const int g = __builtin_amdgcn_readfirstlane(slot / (uint32_t)p.Pr);
+  const int q = (int)slot - g * p.Pr;
   const int ct_lo = (int)(((uint32_t)g * (uint32_t)p.nCT) / (uint32_t)p.Pc);
   const int ct_hi = (int)(((uint32_t)(g + 1) * (uint32_t)p.nCT) / (uint32_t)p.Pc);
   if (ct_hi <= ct_lo || q >= p.nRB) return;  // uniform over the workgroup
