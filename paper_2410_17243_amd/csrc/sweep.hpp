@@ -44,9 +44,15 @@ __host__ __device__ __forceinline__ uint32_t sweep_dma_kk_off(int kk, int wave, 
 }
 
 // Resource of one swept tile: `rem` rows of rowg bytes are left from base on
-// (rem <= 0: none; loads past the end give zeros).  Scalar arithmetic only: a
-// clamp of 64-bit byte counts, or a min and max the compiler fuses, would run
-// on the vector unit.
+// (rem <= 0: none; loads past the end give zeros).  The kernels leave the
+// masking of rows past the end to the resource's range check, with part of the
+// offset in the scalar operand.  On gfx950 the check of a raw (stride 0)
+// resource counts it: a lane's 16 bytes are loaded if vector offset + scalar
+// offset + 16 <= num_records, and are zeros otherwise, without wrapping (also
+// at num_records = 0 with a scalar offset), into registers and into LDS alike
+// (measured for num_records 0 to 20000 against scalar offsets 0 to 16384).
+// Scalar arithmetic only: a clamp of 64-bit byte counts, or a min and max the
+// compiler fuses, would run on the vector unit.
 __device__ __forceinline__ u32x4 sweep_tile_rsrc(const void* base, int rem, int rowg) {
   int n = rem > kSweepBN ? kSweepBN : rem;
   asm("" : "+s"(n));
