@@ -472,8 +472,9 @@ __global__ void __launch_bounds__(256) dscale_finish(const double* part, int64_t
 // gradient type.  Bound by memory (the partials are read once, 16 bytes per
 // lane; at most 64 MiB of them, which stay in the last-level cache: 12 us).
 // One more workgroup (the last grid row) sums dscale: as a launch of its own
-// that took 4.7 us.
-template <bool G16, bool F16, bool SC = F16>
+// that took 4.7 us.  F32: the sums of fp32 inputs, whose alpha is divided out
+// of them as bwd_f32 does (with F16 it is part of the factor).
+template <bool G16, bool F16, bool F32 = false>
 __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, float* dscale, double* dscale64) {
   using GO = GradOut<G16, F16>;
   if (blockIdx.y == gridDim.y - 1) {
@@ -490,7 +491,8 @@ __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, 
   const int64_t row = (int64_t)(sd ? blk - p.nblk : blk) * bm + rl;  // own row - own_off
   const float s = p.scale[0];
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  const float kfin = dl * s / (2.0f * (float)p.b) * (SC ? ldexpf(1.f, -g16_exponent(p.g16)) : 1.0f);
+  const float g16inv = F16 || F32 ? ldexpf(1.f, -g16_exponent(p.g16)) : 1.0f;
+  const float kfin = dl * s / (2.0f * (float)p.b) * (F16 ? g16inv : 1.0f);
   if (e >= per || row >= p.own_end - p.own_off) return;
   const f32x4* src = (const f32x4*)(p.part + (int64_t)q * p.ns * per * 4) + e;
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
@@ -506,7 +508,7 @@ __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, 
   typedef typename GO::type out4 __attribute__((ext_vector_type(4)));
   out4 o;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) o[u] = GO::cvt(kfin * a[u]);
+  for (int u = 0; u < 4; ++u) o[u] = GO::cvt(kfin * (F32 ? g16inv * a[u] : a[u]));
   *(out4*)((typename GO::type*)p.side[sd].dOwn + row * p.d + 4 * (e - rl * c4)) = o;
 }
 

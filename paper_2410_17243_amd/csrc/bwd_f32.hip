@@ -64,11 +64,13 @@ __global__ void __launch_bounds__(256, 1) bwd_f32(BwdParams p) {
   const float k2 = s * kLog2e;
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
 
-  // G' is split into bf16 parts too: scaled by alpha = 2^g16e before (divided
-  // out at the end), so that the low parts of small weights stay normal
+  // G' is split into bf16 parts too: scaled by alpha = 2^g16e before, so that
+  // the low parts of small weights stay normal.  alpha is divided out of the
+  // sums and not of kfin, which is small by itself (dloss, 1/2b) and could
+  // leave the normal numbers where the gradients do not.
   const int g16e = g16_exponent(p.g16);
-  const float g16a = ldexpf(1.f, g16e);
-  const float kfin = dl * s / (2.0f * (float)p.b) * ldexpf(1.f, -g16e);
+  const float g16a = ldexpf(1.f, g16e), g16inv = ldexpf(1.f, -g16e);
+  const float kfin = dl * s / (2.0f * (float)p.b);
 
   // own operand: row irow, features 16 (2 s2 + kh) + 8h .. +8
   split3 ownf[KH];
@@ -297,7 +299,7 @@ __global__ void __launch_bounds__(256, 1) bwd_f32(BwdParams p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int64_t row = own0 + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (all_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 64 * fb] = kfin * dacc[fb][r];
+        if (all_ok || row < p.own_end) dst[(8 * (r >> 2) + (r & 3)) * D + 64 * fb] = kfin * (g16inv * dacc[fb][r]);
       }
   }
 

@@ -63,3 +63,20 @@ def test_full_mantissas():
     e = rng.integers(-6, -3, size=(2, b, d))
     img, txt = (full * sgn * np.exp2(e.astype(np.float32))).astype(np.float32)
     _check(img, txt, f32_scale(4.0), d, 1e-5)
+
+
+@pytest.mark.parametrize("b,d", [(300, 128), (8192, 64)])  # split row blocks and the reduction; whole row blocks
+def test_tiny_upstream_gradient(b, d):
+    """A power of two in dloss scales the gradients exactly (where they are
+    normal numbers): the power of two that G' carries is divided out of the
+    sums, not of the factor dloss s / 2b, which it would make subnormal."""
+    e = -112
+    img, txt = synth.clip_pairs(b, d, 1.0, seed=b, dtype="f32")
+    one, tiny = (run(img, txt, "f32", f32_scale(14.29), dloss=v) for v in (1.0, 2.0 ** e))
+    for k in ("dI", "dT"):
+        want = one[k] * 2.0 ** e
+        normal = np.abs(want) >= 2.0 ** -126
+        print(f"b={b} {k}: {normal.mean():.3f} normal, "
+              f"max rel {np.max(np.abs(tiny[k] - want)[normal] / np.abs(want)[normal]):.2e}", flush=True)
+        assert normal.mean() > 0.5
+        assert np.array_equal(tiny[k][normal], want[normal])
