@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(256) bwd_reduce(BwdParams p, int bm, int nwg, 
   const int64_t row = (int64_t)(sd ? blk - p.nblk : blk) * bm + rl;  // own row - own_off
   const float s = p.scale[0];
   const float dl = p.dloss ? p.dloss[0] : 1.0f;
-  const float g16inv = F16 || F32 ? ldexpf(1.f, -g16_exponent(p.g16)) : 1.0f;
+  const float g16inv = F16 || F32 ? ldexpf(1.f, -g16_exponent<F32 ? 0 : 14>(p.g16)) : 1.0f;
   const float kfin = dl * s / (2.0f * (float)p.b) * (F16 ? g16inv : 1.0f);
   if (e >= per || row >= p.own_end - p.own_off) return;
   const f32x4* src = (const f32x4*)(p.part + (int64_t)q * p.ns * per * 4) + e;

@@ -96,6 +96,11 @@ constexpr int kWideBM = 64;  // own rows per workgroup of the wide-row sweeps
 // bwd_prep leaves the two maxima of each of its kPrepBlocks blocks; every wave
 // that needs alpha reduces them itself (one pair per lane).
 constexpr int kPrepBlocks = 64;
+// TOP: alpha B lies in [2^(TOP-1), 2^TOP).  fp32 inputs scale G' too, for its
+// bf16 parts (the third is 2^-17 of a weight or less), and take TOP = 0: with
+// bf16's exponents there is nothing to gain above 1, and larger weights would
+// take the sums of large entries past the largest float.
+template <int TOP = 14>
 __device__ __forceinline__ int g16_exponent(const float* part) {
   const int lane = __lane_id();
   float mr = part[2 * lane], mc = part[2 * lane + 1];
@@ -108,8 +113,8 @@ __device__ __forceinline__ int g16_exponent(const float* part) {
   int k = 0;
   if (B > 0.f) {
     int e;
-    (void)frexpf(B, &e);  // B = m 2^e, m in [0.5, 1): alpha B = m 2^14 < 2^14
-    k = 14 - e;
+    (void)frexpf(B, &e);  // B = m 2^e, m in [0.5, 1): alpha B = m 2^TOP < 2^TOP
+    k = TOP - e;
     k = k > 100 ? 100 : k;
   }
   return __builtin_amdgcn_readfirstlane(k);

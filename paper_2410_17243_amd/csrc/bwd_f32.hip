@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(256, 1) bwd_f32(BwdParams p) {
   // the low parts of small weights stay normal.  alpha is divided out of the
   // sums and not of kfin, which is small by itself (dloss, 1/2b) and could
   // leave the normal numbers where the gradients do not.
-  const int g16e = g16_exponent(p.g16);
+  const int g16e = g16_exponent<0>(p.g16);
   const float g16a = ldexpf(1.f, g16e), g16inv = ldexpf(1.f, -g16e);
   const float kfin = dl * s / (2.0f * (float)p.b);
 

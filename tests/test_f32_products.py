@@ -80,3 +80,30 @@ def test_tiny_upstream_gradient(b, d):
               f"max rel {np.max(np.abs(tiny[k] - want)[normal] / np.abs(want)[normal]):.2e}", flush=True)
         assert normal.mean() > 0.5
         assert np.array_equal(tiny[k][normal], want[normal])
+
+
+@pytest.mark.parametrize("b,d", [(700, 128), (8192, 64)])
+@pytest.mark.parametrize("big", [2.0 ** 127])
+def test_large_entries(b, d, big):
+    """The power of two that G' carries must not take finite sums past the
+    largest float.  One entry of each
+    column is large (in a row that finds its text, |G'_ii| < 1) and the others
+    are below 2^122, so that no sum overflows by itself; the fp32 result then
+    carries fp32 rounding only."""
+    rng = np.random.default_rng(b)
+    img, txt = synth.clip_pairs(b, d, 1.0, seed=b, dtype="f32")
+    img = (img * np.float32(2.0 ** 121)).astype(np.float32)
+    rows = rng.choice(b, size=d, replace=False)
+    sgn = rng.choice([-1.0, 1.0], size=d).astype(np.float32)
+    img[rows, np.arange(d)] = np.float32(big) * sgn
+    txt[rows, np.arange(d)] = 0.9 * sgn
+    txt = (txt * np.float32(2.0 ** -100)).astype(np.float32)
+    s, dl = f32_scale(2.0 ** -24), 2.0 ** 24
+    ref, dI, dT, ds = oracle.forward_backward(img.astype(np.float64), txt.astype(np.float64), s)
+    g = run(img, txt, "f32", s, dloss=dl)
+    print(f"b={b} loss {g['loss64']:.9e} ref {ref['loss']:.9e} dI {max_rel(g['dI'], dl * dI):.2e} "
+          f"dT {max_rel(g['dT'], dl * dT):.2e} ds {g['dscale']:.6e} ref {dl * ds:.6e}", flush=True)
+    assert np.max(np.abs(dT)) * 2 * b / s < 3e38  # the sum before the factor s / 2b
+    assert g["loss64"] == pytest.approx(ref["loss"], rel=1e-5)
+    assert max_rel(g["dI"], dl * dI) <= 1e-4 and max_rel(g["dT"], dl * dT) <= 1e-4
+    assert g["dscale"] == pytest.approx(dl * ds, rel=1e-4)
