@@ -44,6 +44,7 @@ __global__ void __launch_bounds__(256, 1) bwd_f32(BwdParams p) {
   __shared__ __attribute__((aligned(16))) float xg_[4][64][8];  // G'
   INFCL_LDS char* const planes = (INFCL_LDS char*)planes_;
 
+  split_limit_parts();
   const int lane = __lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ob = wave >> 1, kh = wave & 1;

@@ -322,6 +322,7 @@ __global__ void __launch_bounds__(256, 2) fwd_sweep(FwdParams p) {
   __shared__ __attribute__((aligned(1024))) char lds_[2 * T::StageBytes];
   INFCL_LDS char* lds0 = (INFCL_LDS char*)lds_;
   INFCL_LDS char* lds1 = lds0 + T::StageBytes;
+  split_limit_parts();
   const int lane = __lane_id();
   const int wave = threadIdx.x >> 6;
   const int l32 = lane & 31, h = lane >> 5;

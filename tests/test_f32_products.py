@@ -83,10 +83,11 @@ def test_tiny_upstream_gradient(b, d):
 
 
 @pytest.mark.parametrize("b,d", [(700, 128), (8192, 64)])
-@pytest.mark.parametrize("big", [2.0 ** 127])
+@pytest.mark.parametrize("big", [2.0 ** 127, 3.4028235e38])
 def test_large_entries(b, d, big):
     """The power of two that G' carries must not take finite sums past the
-    largest float.  One entry of each
+    largest float, and entries from 2^128 - 2^119 on, which round to
+    an infinite bf16, have the largest bf16 as their first part.  One entry of each
     column is large (in a row that finds its text, |G'_ii| < 1) and the others
     are below 2^122, so that no sum overflows by itself; the fp32 result then
     carries fp32 rounding only."""
