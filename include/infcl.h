@@ -21,8 +21,10 @@
  *     16-bit MFMA with fp32 accumulation, and the backward rounds its
  *     gradient weights (the softmax terms) to the input type, round to
  *     nearest even, before the second product; f32 inputs and weights enter
- *     the products in full (each as three bf16 parts that add up to it, the
- *     parts' products exact and accumulated in fp32).
+ *     the products as three bf16 parts that add up to them (exactly for
+ *     magnitudes from 2^-110 on, to within 2^-134 below), the parts' products
+ *     exact and accumulated in fp32; the products of the lowest parts, together
+ *     at most 2^-24 of the full product, are left out.
  *     They are used exactly as given (no normalisation inside the loss).
  *   - scale: device pointer to one float, the logit scale s (1/temperature).
  *   - All float vectors are device pointers, 16-byte aligned.

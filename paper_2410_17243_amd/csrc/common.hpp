@@ -69,11 +69,15 @@ __device__ __forceinline__ float from16(__bf16 x) {
 }
 // An fp32 operand fragment as three bf16 fragments, x = p0 + p1 + p2: each
 // part is the remainder so far rounded to nearest, and the remainders are exact,
-// so the parts carry x's 24 bits (8 + 8 + 8, with the signs).  A product of two
-// such operands is six bf16 MFMAs (mfma_split): the three products left out,
-// p1 q2, p2 q1 and p2 q2, are below 2^-25 of the full one, less than fp32's own
-// rounding of it, and every bf16 product is exact in the fp32 accumulator.  Six
-// 32x32x16 bf16 MFMAs take 192 cycles where eight 32x32x2 fp32 ones take 512.
+// so the parts carry x's 24 bits (8 + 8 + 8, with the signs).  The parts of
+// magnitudes below 2^-110 are subnormal; the conversion and the MFMA keep those,
+// down to 2^-133, so that such an x is right to within 2^-134.  A product of two
+// operands is six bf16 MFMAs (mfma_split): of the three products left out,
+// p1 q2 and p2 q1 reach 2^-25 of the full one each, all three 2^-24 (over random
+// mantissas 2^-27.5 in the root mean square, 2^-26.5 next to 1), as much as
+// fp32's own rounding of it; every bf16 product is exact in the fp32
+// accumulator.  Six 32x32x16 bf16 MFMAs take 192 cycles where eight 32x32x2 fp32
+// ones take 512.
 struct split3 {
   bf16x8 p[3];
 };

@@ -1,8 +1,9 @@
 """fp32 inputs: products of three-part bf16 operands against the fp64 oracle.
 
-The parts of an fp32 number add up to it exactly and the part products left
-out are below 2^-25 of the full product, so the results carry fp32 rounding
-only: the log-sum-exp bound of gpu_util.lse_tol, and for the gradients 1e-5 of
+The parts of an fp32 number add up to it exactly (of magnitudes from 2^-110 on;
+below, to within 2^-134) and the part products left out are at most 2^-24 of
+the full product, as much as fp32's own rounding of it, so the results carry
+fp32 rounding only: the log-sum-exp bound of gpu_util.lse_tol, and for the gradients 1e-5 of
 their maximum (fp32 accumulation over up to 3300 terms, 2^-24 sqrt(3300) =
 3.4e-6, and the exponents' own rounding, 2^-24 |y| ln 2 with |y| up to 144 at
 s = 100, which 1e-4 covers there).  Shapes: both tile shapes of the forward (32 x 128
@@ -108,3 +109,23 @@ def test_large_entries(b, d, big):
     assert g["loss64"] == pytest.approx(ref["loss"], rel=1e-5)
     assert max_rel(g["dI"], dl * dI) <= 1e-4 and max_rel(g["dT"], dl * dT) <= 1e-4
     assert g["dscale"] == pytest.approx(dl * ds, rel=1e-4)
+
+
+@pytest.mark.parametrize("e", [-104, -116])
+def test_tiny_entries(e):
+    """Parts of entries below 2^-110 are subnormal, which the conversion and the
+    MFMA keep: each entry is right to within 2^-134, so an exponent is right to
+    within s 2^-134 times its text row's 1-norm (at most sqrt(d) for unit rows)."""
+    b, d = 500, 128
+    img, txt = synth.clip_pairs(b, d, 1.0, seed=11, dtype="f32")
+    img = (img * np.float32(2.0 ** e)).astype(np.float32)
+    s = f32_scale(14.29 * 2.0 ** -e)
+    ref, dI, dT, ds = oracle.forward_backward(img.astype(np.float64), txt.astype(np.float64), s)
+    g = run(img, txt, "f32", s)
+    dx = s * np.sqrt(d) * 2.0 ** -134
+    print(f"e={e} dx {dx:.2e} lse {np.max(np.abs(g['lse_r'] - ref['lse_r'])):.2e} dI {max_rel(g['dI'], dI):.2e} "
+          f"dT {max_rel(g['dT'], dT):.2e}", flush=True)
+    for k in ("lse_r", "lse_c"):
+        assert np.all(np.abs(g[k] - ref[k]) <= lse_tol(14.29, d, ref[k]) + dx)
+    # a weight's relative error is at most that of its two exponents, 2 dx each
+    assert max_rel(g["dI"], dI) <= 1e-5 + 4 * dx and max_rel(g["dT"], dT) <= 1e-5 + 4 * dx
