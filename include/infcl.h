@@ -45,7 +45,9 @@
  *     padded buffers there.  Zero features change no dot product: every
  *     output is exactly that of the unpadded inputs.
  *   - Results are bitwise reproducible for a given (b, d, dtype): no atomics,
- *     all reductions run in a fixed order.
+ *     all reductions run in a fixed order.  (Gradients: with any workspace from
+ *     infcl_workspace_size on, or of a given smaller size; a shard's, of a given
+ *     size.)
  *   - The calls may be captured into a HIP graph: they enqueue kernels only
  *     (no allocation, no memset or copy nodes, no host synchronisation), and
  *     replays give the bits of the eager calls.
@@ -64,7 +66,7 @@ typedef enum {
   INFCL_OK = 0,
   INFCL_ERR_INVALID = 1,     /* NULL/misaligned pointer, b < 1, d < 1, bad dtype */
   INFCL_ERR_UNSUPPORTED = 2, /* valid but not implemented shape (see above)      */
-  INFCL_ERR_WORKSPACE = 3,   /* workspace smaller than infcl_workspace_size()    */
+  INFCL_ERR_WORKSPACE = 3,   /* workspace too small (see infcl_workspace_size)    */
   INFCL_ERR_HIP = 4          /* a kernel launch failed                           */
 } infcl_status;
 
@@ -72,14 +74,24 @@ typedef enum {
  * (AMP) training, under which the paper trains (Sec. 4.1). */
 typedef enum { INFCL_BF16 = 0, INFCL_F32 = 1, INFCL_F16 = 2 } infcl_dtype;
 
-/* Bytes of device workspace that infcl_fwd / infcl_bwd need for (b, d, dtype).
- * The same workspace size serves both calls.  It is linear in b: a few
+/* Partial gradient sums: row blocks of the backward that would leave compute
+ * units idle are swept in several parts, whose fp32 sums take at most
+ * INFCL_SPLIT_BYTES of workspace (256 parts of 128 rows x 512 features or 64 x
+ * 1024, and their dscale partials).  infcl_workspace_size includes that much for
+ * batches up to INFCL_SPLIT_BATCH, of which a shard may want all of it. */
+#define INFCL_SPLIT_BYTES (((size_t)64 << 20) + 4096)
+#define INFCL_SPLIT_BATCH 32768
+
+/* Bytes of device workspace for infcl_fwd / infcl_bwd at (b, d, dtype): a few
  * vectors of b floats, plus, when d is not a multiple of 128 (16-bit) or 64
  * (f32), the padded copies of img and txt and the padded gradients
- * (2 b d' fp32 elements, d' the padded width), plus at most 64 MiB of
- * partial gradient sums where row blocks are swept in several parts (small
- * batches, and the remainder of a batch beyond whole rounds of the compute
- * units).  Returns INFCL_ERR_INVALID for
+ * (2 b d' fp32 elements, d' the padded width), plus at most INFCL_SPLIT_BYTES
+ * of partial gradient sums.  Linear in b apart from those, which smaller batches
+ * want more of: the size can be less for a larger batch.  The calls accept less
+ * than this size: what it gives for any larger batch (same d and dtype) always
+ * serves.  With less room the backward splits less, or not at all, and is
+ * slower; its results are the same terms summed in another order.  More room
+ * changes nothing for a whole batch.  Returns INFCL_ERR_INVALID for
  * a NULL `bytes` or b < 1, d < 1 or an unknown dtype. */
 infcl_status infcl_workspace_size(int64_t b, int64_t d, int dtype, size_t* bytes);
 

@@ -52,28 +52,27 @@ struct Layout {
   size_t pad, pairs, udiag, ref2, fwd_part;
   size_t fwd_total;  // the forward's share, from the start
   size_t lse2, bwd_part, g16, gpad;
-  size_t part, part_bytes;  // the backward's partial sums
-  size_t total;
+  size_t base;   // least workspace the calls accept
+  size_t total;  // infcl_workspace_size: with the room for partial sums
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-// Most bytes of partial gradient sums a backward may use: 256 workgroups x 128
-// rows x 512 features x 4 bytes (or 64 rows x 1024), one part for every
-// compute unit.
-constexpr size_t kPartBytes = ((size_t)64 << 20) + 4096;
 
 // Workspace regions, sized for the sweeps that (b, d, dtype) launches.  The
 // forward's: the padded copies of the inputs, the partial pairs of its grid,
 // the diagonal, the base-2 diagonal references (resident rows only) and the
 // loss partials.  The backward's: the base-2 log-sum-exp vectors, the dscale
-// partials, fp16's G' scale, the padded gradients, and the partial sums of
-// split row blocks; those take the place of the forward's pairs, which the
-// backward no longer needs, enlarged to kPartBytes (or to what the split of
-// so small a batch can use) for batches up to 32768, whose row blocks, or a
-// shard's, leave compute units idle.  A shard uses the same regions: its
-// forward leaves at most as many pairs and it splits its row blocks as far as
-// the place allows.
+// partials, the scale of G', the padded gradients, and the partial sums of
+// split row blocks (part_room).  A shard uses the same regions: its forward
+// leaves at most as many pairs and it splits its row blocks as far as the room
+// allows.
+// base, without room for partial sums beyond the forward's pairs, grows with
+// b, so that a workspace for one batch serves every smaller one.  total adds
+// what the split of the batch uses, and for batches up to INFCL_SPLIT_BATCH
+// INFCL_SPLIT_BYTES (or what the split of so small a batch can use), so that
+// their shards split too: 8 shards of b = 32768, d = 512 15.3 -> 5.4 ms.  Beyond, it
+// stays at 336 (780) bytes per sample, the memory that a loss linear in b
+// promises, and a shard's caller adds the room where it wants it.
 Layout make_layout(int64_t b, int64_t d, int dtype) {
   Layout L;
   L.dk = kernel_width(d, dtype);
@@ -91,25 +90,31 @@ Layout make_layout(int64_t b, int64_t d, int dtype) {
   L.bwd_part = off; off = align256(off + (size_t)2 * ((b + 63) / 64) * sizeof(double));  // 64 or 128 rows per WG
   L.g16 = off; off = align256(off + (dtype != INFCL_BF16 ? (size_t)(2 * infcl::kPrepBlocks) * sizeof(float) : 0));
   L.gpad = off; off = align256(off + (L.dk != d ? 2 * (size_t)b * (size_t)L.dk * sizeof(float) : 0));  // dimg, dtxt
-  // partial sums: in place of the pairs, or, where those are too few, at the end
-  L.part = L.pairs;
-  L.part_bytes = L.fwd_total - L.pairs;
-  if (L.part_bytes > kPartBytes) L.part_bytes = kPartBytes;
+  L.base = off;
   size_t want = 0;
-  if (b <= 32768) {
+  if (b <= INFCL_SPLIT_BATCH) {
     const size_t ntile = (size_t)(b + 31) / 32;
     want = 2 * (size_t)(b + 127) / 128 * 128 * (size_t)L.dk * sizeof(float) * ntile + 4096;  // every tile its part
-    if (want > kPartBytes) want = kPartBytes;
+    if (want > INFCL_SPLIT_BYTES) want = INFCL_SPLIT_BYTES;
   } else {
-    want = align256(infcl::plan_bwd(b, b, L.dk, dtype, kPartBytes).part_bytes);
+    want = align256(infcl::plan_bwd(b, b, L.dk, dtype, INFCL_SPLIT_BYTES).part_bytes);
   }
-  if (want > L.part_bytes) {
-    L.part = off;
-    L.part_bytes = want;
-    off = align256(off + want);
-  }
-  L.total = off;
+  L.total = want > L.fwd_total - L.pairs ? align256(off + want) : off;
   return L;
+}
+
+// Where the backward keeps partial sums in a workspace of ws_bytes >= L.base:
+// at its end, or, where less than the forward's pairs is left there, in their
+// place (the backward no longer needs them).  A whole batch takes at most what
+// it would with L.total, so that any workspace from that on gives the same bits.
+struct PartRoom {
+  size_t off, bytes;
+};
+PartRoom part_room(const Layout& L, size_t ws_bytes) {
+  PartRoom r{L.base, ws_bytes - L.base};
+  if (r.bytes <= L.fwd_total - L.pairs) r = PartRoom{L.pairs, L.fwd_total - L.pairs};
+  if (r.bytes > INFCL_SPLIT_BYTES) r.bytes = INFCL_SPLIT_BYTES;
+  return r;
 }
 
 // What infcl_fwd_noalloc's fixed scratch is measured by: the workspace of a
@@ -258,7 +263,7 @@ infcl_status infcl_fwd(const void* img, const void* txt, int64_t b, int64_t d, i
   if (loss64 != nullptr && ((uintptr_t)loss64 % 8) != 0) return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype)) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (ws_bytes < L.total) return INFCL_ERR_WORKSPACE;
+  if (ws_bytes < L.base) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   int rc = infcl::launch_fwd(img, txt, b, L.dk, dtype, scale, loss, loss64, lse_r, lse_c, aux, (hipStream_t)stream,
@@ -298,15 +303,16 @@ infcl_status infcl_bwd(const void* img, const void* txt, int64_t b, int64_t d, i
   if (dloss != nullptr && ((uintptr_t)dloss % 4) != 0) return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype) || gk < 0) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (ws_bytes < L.total) return INFCL_ERR_WORKSPACE;
+  if (ws_bytes < L.base) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   const size_t ges = gk ? 2 : 4;
   void *gi = dimg, *gt = dtxt;
   grad_targets(gi, gt, b, d, ges, ws, L);
+  const PartRoom room = part_room(L, ws_bytes);
   int rc = infcl::launch_bwd(img, txt, b, L.dk, dtype, 0, b, scale, lse_r, lse_c, aux, dloss, gi, gt, gk, dscale,
                              nullptr, (float*)(ws + L.lse2), (double*)(ws + L.bwd_part), (float*)(ws + L.g16),
-                             (float*)(ws + L.part), L.part_bytes, (hipStream_t)stream);
+                             (float*)(ws + room.off), room.bytes, (hipStream_t)stream);
   if (rc == 2) return INFCL_ERR_UNSUPPORTED;
   if (rc == 0 && !unstage_grads(dimg, dtxt, b, b, d, ges, ws, L, (hipStream_t)stream)) rc = 1;
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
@@ -323,7 +329,7 @@ infcl_status infcl_fwd_shard(const void* img, const void* txt, int64_t b, int64_
     return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype)) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (ws_bytes < L.total) return INFCL_ERR_WORKSPACE;
+  if (ws_bytes < L.base) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   int rc = infcl::launch_fwd_shard(img, txt, b, L.dk, dtype, r0, bs, scale, colpair, (hipStream_t)stream,
@@ -340,7 +346,7 @@ infcl_status infcl_fwd_shard_finish(int64_t b, int64_t d, int dtype, int64_t r0,
     return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype)) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (ws_bytes < L.total) return INFCL_ERR_WORKSPACE;
+  if (ws_bytes < L.base) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   int rc = infcl::launch_fwd_shard_finish(b, L.dk, dtype, r0, bs, nparts, colpairs, scale, lse_r, lse_c, aux, loss_part,
                                           (hipStream_t)stream, (float*)(ws + L.pairs),
@@ -361,15 +367,16 @@ infcl_status infcl_bwd_shard(const void* img, const void* txt, int64_t b, int64_
   if (dloss != nullptr && ((uintptr_t)dloss % 4) != 0) return INFCL_ERR_INVALID;
   if (!shape_supported(b, d, dtype) || gk < 0) return INFCL_ERR_UNSUPPORTED;
   const Layout L = make_layout(b, d, dtype);
-  if (ws_bytes < L.total) return INFCL_ERR_WORKSPACE;
+  if (ws_bytes < L.base) return INFCL_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   if (!stage_inputs(img, txt, b, d, dtype, ws, L, (hipStream_t)stream)) return INFCL_ERR_HIP;
   const size_t ges = gk ? 2 : 4;
   void *gi = dimg, *gt = dtxt;
   grad_targets(gi, gt, b, d, ges, ws, L);
+  const PartRoom room = part_room(L, ws_bytes);
   int rc = infcl::launch_bwd(img, txt, b, L.dk, dtype, r0, bs, scale, lse_r, lse_c, aux, dloss, gi, gt, gk, nullptr,
                              dscale_part, (float*)(ws + L.lse2), (double*)(ws + L.bwd_part), (float*)(ws + L.g16),
-                             (float*)(ws + L.part), L.part_bytes, (hipStream_t)stream);
+                             (float*)(ws + room.off), room.bytes, (hipStream_t)stream);
   if (rc == 2) return INFCL_ERR_UNSUPPORTED;
   if (rc == 0 && !unstage_grads(dimg, dtxt, bs, b, d, ges, ws, L, (hipStream_t)stream)) rc = 1;
   return rc == 0 ? INFCL_OK : INFCL_ERR_HIP;
@@ -382,7 +389,7 @@ const char* infcl_status_str(int status) {
     case INFCL_ERR_UNSUPPORTED:
       return "unsupported shape (bf16, f16: d a multiple of 8 up to 1024; f32: d a multiple of 4 up to 512; "
              "b <= 2^30) or gradient type (f32, or the inputs' 16-bit type)";
-    case INFCL_ERR_WORKSPACE: return "workspace smaller than infcl_workspace_size()";
+    case INFCL_ERR_WORKSPACE: return "workspace too small (see infcl_workspace_size)";
     case INFCL_ERR_HIP: return "HIP kernel launch failed";
     default: return "unknown status";
   }
