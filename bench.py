@@ -250,7 +250,7 @@ def main():
         from paper_2410_17243_amd import shards as shd
 
         del ws
-        sws = [infcl.workspace_for(img) for _ in shd.shard_bounds(b, a.shards)]
+        sws = [infcl.workspace_for(img, shard=True) for _ in shd.shard_bounds(b, a.shards)]
         sh_out = {"lse_r": lse_r, "lse_c": lse_c, "aux": aux, "dimg": dimg, "dtxt": dtxt}
 
         def step(ev=None):  # noqa: F811

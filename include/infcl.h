@@ -151,6 +151,9 @@ infcl_status infcl_bwd(const void* img, const void* txt, int64_t b, int64_t d, i
  * (INFCL_ERR_INVALID otherwise).  The workspace is that of
  * infcl_workspace_size(b, d, dtype); infcl_fwd_shard_finish must get the same
  * workspace as the infcl_fwd_shard call of its shard, untouched in between.
+ * For b > INFCL_SPLIT_BATCH, INFCL_SPLIT_BYTES more let infcl_bwd_shard split
+ * the row blocks of a shard that would leave compute units idle (8 shards of
+ * b = 65536, d = 512 bf16, one shard's backward 2.96 -> 1.79 ms).
  * With one shard (r0 = 0, bs = b) the three calls compute what infcl_fwd
  * and infcl_bwd compute. */
 

@@ -30,6 +30,7 @@ ABLATION_HEADER_PATH = os.path.join(os.path.dirname(_PKG), "include", "infcl_abl
 
 INFCL_OK, INFCL_ERR_INVALID, INFCL_ERR_UNSUPPORTED, INFCL_ERR_WORKSPACE, INFCL_ERR_HIP = range(5)
 INFCL_BF16, INFCL_F32, INFCL_F16 = 0, 1, 2
+INFCL_SPLIT_BYTES, INFCL_SPLIT_BATCH = (64 << 20) + 4096, 32768
 
 _lib = None
 
@@ -218,11 +219,16 @@ def _check_workspace(ws, dev):
         raise ValueError(f"workspace must be a contiguous uint8 tensor on {dev}, got {ws.dtype} on {ws.device}")
 
 
-def workspace_for(img):
+def workspace_for(img, shard=False):
+    """A workspace for img's batch; with shard, one for a shard of it: with all
+    the room for partial gradient sums that a shard's row blocks can use, which
+    the size of a batch above INFCL_SPLIT_BATCH does not include."""
     import torch
 
     b, d = img.shape
     n = infcl_workspace_size(b, d, _dtype_code(img))
+    if shard and b > INFCL_SPLIT_BATCH:
+        n += INFCL_SPLIT_BYTES
     return torch.empty(max(n, 256), dtype=torch.uint8, device=img.device)
 
 

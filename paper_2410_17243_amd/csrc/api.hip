@@ -72,7 +72,9 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // INFCL_SPLIT_BYTES (or what the split of so small a batch can use), so that
 // their shards split too: 8 shards of b = 32768, d = 512 15.3 -> 5.4 ms.  Beyond, it
 // stays at 336 (780) bytes per sample, the memory that a loss linear in b
-// promises, and a shard's caller adds the room where it wants it.
+// promises, and a shard's caller adds the room where it wants it (8 shards,
+// d = 512: b = 32800 13.6 ms without it and 5.9 with, b = 65536 28.5 and 19.0;
+// d = 256, b = 65536 19.3 and 11.7).
 Layout make_layout(int64_t b, int64_t d, int dtype) {
   Layout L;
   L.dk = kernel_width(d, dtype);

@@ -45,14 +45,15 @@ def sharded_forward_backward(img, txt, scale, n: int, dloss=None, on_step=None, 
 
     on_step(name), if given, is called after each shard call is enqueued (e.g.
     to synchronise and report progress on very large batches).  workspaces (one
-    per shard) and out (a previous result) may be passed to reuse buffers."""
+    per shard, workspace_for(img, shard=True)) and out (a previous result) may be
+    passed to reuse buffers."""
     import torch
 
     b, d = img.shape
     dev = img.device
     dt = _dtype_code(img)
     bounds = shard_bounds(b, n)
-    ws = workspaces if workspaces is not None else [workspace_for(img) for _ in bounds]
+    ws = workspaces if workspaces is not None else [workspace_for(img, shard=True) for _ in bounds]
     note = on_step or (lambda name: None)
     # 1. local sweeps: one pair per column over each shard's rows
     colpair = [torch.empty(2 * b, dtype=torch.float32, device=dev) for _ in bounds]

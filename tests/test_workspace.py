@@ -74,3 +74,30 @@ def test_smaller_batch_in_a_kept_workspace(b, big, d, dtype):
     # G' is formed alike; its fp32 sums of up to b terms are taken in another order
     assert max(errs) <= 1e-5
     assert bool((buf[n:] == 0xA5).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("b,n,d,dtype", [(33000, 8, 256, "bf16"), (34001, 16, 640, "f16")])
+def test_shards_above_the_split_batch(b, n, d, dtype):
+    """With workspace_for(shard=True) the shards' row blocks split; the results
+    are those of the whole batch."""
+    import torch
+
+    from gpu_util import device_inputs, f32_scale, max_rel, synth
+    from paper_2410_17243_amd.shards import sharded_forward_backward
+
+    img, txt = device_inputs(*synth.clip_pairs(b, d, 1.0, seed=b + d, dtype=dtype), dtype)
+    sc = torch.tensor([f32_scale(14.29)], dtype=torch.float32, device="cuda")
+    f = infcl.clip_loss_fwd(img, txt, sc)
+    dI, dT, ds = infcl.clip_loss_bwd(img, txt, sc, f)
+    size = infcl.workspace_for(img, shard=True).numel()
+    bufs = [torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(n)]
+    r = sharded_forward_backward(img, txt, sc.reshape(()), n, workspaces=[w[:size] for w in bufs])
+    torch.cuda.synchronize()
+    errs = [max_rel(x.double().cpu().numpy(), y.double().cpu().numpy())
+            for x, y in ((r["dimg"], dI), (r["dtxt"], dT), (r["dscale64"], ds), (r["loss64"], f["loss64"]))]
+    print(f"b={b} n={n} d={d} {dtype}: {errs}", flush=True)
+    # G' of a shard differs by the rounding of its log-sum-exp values, which another
+    # grid merges in another order: 2^-23 |lse| at |lse| up to 15
+    assert max(errs) <= 2e-5
+    assert all(bool((w[size:] == 0xA5).all()) for w in bufs)
