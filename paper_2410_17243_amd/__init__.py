@@ -287,7 +287,9 @@ def _make_function():
     # A small batch's step is bound by host time, so the function marshals its
     # arguments itself: the per-sample outputs in one allocation (lse_r, lse_c
     # and aux, each 16-byte aligned) and plain addresses (b = 256, d = 512:
-    # 185 -> 150 us per step).
+    # 185 -> 150 us per step).  Each pass has a workspace of its own, so that a
+    # loss whose backward is still to come holds its statistics only (kept by
+    # the context, the workspace is 64 MiB per pending loss at b = 1000, d = 512).
     class ClipLoss(torch.autograd.Function):
         @staticmethod
         def forward(ctx, img, txt, scale):
@@ -303,7 +305,7 @@ def _make_function():
                                              loss.data_ptr(), None, p, p + 4 * n, p + 8 * n, ws.data_ptr(), ws.numel(),
                                              _raw_stream(dev)), "infcl_fwd")
             ctx.save_for_backward(img, txt, scale, stats)
-            ctx.ws = ws
+            ctx.ws_bytes = ws.numel()
             return loss
 
         @staticmethod
@@ -314,8 +316,6 @@ def _make_function():
             dev = img.device
             n = (b + 3) & ~3
             _check_vec(stats, 2 * n + 3 * b, "the saved statistics", dev)
-            ws = ctx.ws
-            _check_workspace(ws, dev)
             if dloss.device != dev or dloss.numel() != 1:
                 raise ValueError(f"dloss must be one element on {dev}, got {tuple(dloss.shape)} on {dloss.device}")
             if dloss.dtype != torch.float32:
@@ -326,6 +326,7 @@ def _make_function():
             dimg = torch.empty((b, d), dtype=img.dtype, device=dev)
             dtxt = torch.empty((b, d), dtype=img.dtype, device=dev)
             dscale = torch.empty(scale.shape, dtype=torch.float32, device=dev)
+            ws = torch.empty(ctx.ws_bytes, dtype=torch.uint8, device=dev)
             p = stats.data_ptr()
             _check(load_library().infcl_bwd(img.data_ptr(), txt.data_ptr(), b, d, code, scale.data_ptr(), p, p + 4 * n,
                                              p + 8 * n, dloss.data_ptr(), dimg.data_ptr(), dtxt.data_ptr(), code,

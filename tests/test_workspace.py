@@ -101,3 +101,26 @@ def test_shards_above_the_split_batch(b, n, d, dtype):
     # grid merges in another order: 2^-23 |lse| at |lse| up to 15
     assert max(errs) <= 2e-5
     assert all(bool((w[size:] == 0xA5).all()) for w in bufs)
+
+
+@pytest.mark.gpu
+def test_pending_losses_hold_no_workspace():
+    """Losses whose backward is still to come (several batches in flight) keep
+    their per-sample statistics, 20 bytes per sample, not their workspace."""
+    import torch
+
+    from gpu_util import f32_scale
+
+    b, d, pending = 1000, 512, 6
+    x = [torch.nn.functional.normalize(torch.randn(b, d, device="cuda"), dim=1).to(torch.bfloat16) for _ in range(2)]
+    sc = torch.tensor([f32_scale(14.29)], dtype=torch.float32, device="cuda")
+    leaves = [x[0].requires_grad_(), x[1].requires_grad_(), sc.requires_grad_()]
+    ref = torch.autograd.grad(infcl.clip_loss(*leaves), leaves)
+    base = torch.cuda.memory_allocated()
+    losses = [infcl.clip_loss(*leaves) for _ in range(pending)]
+    held = torch.cuda.memory_allocated() - base
+    print(f"{held} bytes held by {pending} pending losses", flush=True)
+    assert held <= pending * (20 * b + 4096)
+    for loss in reversed(losses):
+        for g, r in zip(torch.autograd.grad(loss, leaves), ref):
+            assert torch.equal(g, r)
