@@ -192,9 +192,11 @@ infcl_status infcl_bwd_shard(const void* img, const void* txt, int64_t b, int64_
  * the library's device code, one per device, held until the process ends; its
  * address is looked up (hipGetSymbolAddress) on the first call on each device.
  * No allocation of any kind happens.  The outputs and their meaning are those
- * of infcl_fwd, bit for bit.  Returns INFCL_ERR_WORKSPACE when
- * infcl_workspace_size(b, d, dtype) exceeds 32 MiB (about b = 99,000 for
- * 16-bit inputs, b = 43,000 for f32), INFCL_ERR_HIP if the scratch address
+ * of infcl_fwd, bit for bit.  Returns INFCL_ERR_WORKSPACE when the vectors of
+ * the call, 336 bytes per sample (16-bit inputs) or 780 (f32), plus 12 d' or
+ * 16 d' at a width padded to d', exceed 32 MiB (up to b = 99,768 and b = 43,002
+ * fit at the unpadded widths; infcl_workspace_size does not tell, for it includes
+ * room for partial gradient sums), INFCL_ERR_HIP if the scratch address
  * cannot be obtained.  Every call on one device shares that device's scratch:
  * calls that overlap in time on one device (two streams, two host threads)
  * race and give wrong results; calls in one stream order are safe. */

@@ -47,6 +47,24 @@ def test_refused_workspace(d, dt):
             assert lib.infcl_bwd(A, A, b, d, dt, A, A, A, A, None, A, A, 1, A, A, n, None) == infcl.INFCL_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("d,dt,limit", [(128, 0, 99776), (512, 0, 99776), (1024, 2, 99768), (200, 0, 9844),
+                                        (1000, 0, 2676), (64, 1, 43002), (512, 1, 43002), (100, 1, 11863)])
+def test_noalloc_limit(d, dt, limit):
+    """Which batches the fixed scratch takes is part of the interface, whatever
+    infcl_workspace_size includes for the backward."""
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("made-up addresses: only where nothing can be launched")
+    lib, A = infcl.load_library(), 1 << 20
+    for b in (1, 1000, limit // 2, limit, limit + 1, limit + 300, 2 * limit):
+        st = lib.infcl_fwd_noalloc(A, A, b, d, dt, A, A, A, A, A, A, None)
+        assert st == (infcl.INFCL_ERR_HIP if b <= limit else infcl.INFCL_ERR_WORKSPACE), b
+    dk = -(-d // (64 if dt == 1 else 128)) * (64 if dt == 1 else 128)
+    per = (780 if dt == 1 else 336) + (0 if dk == d else (16 if dt == 1 else 12) * dk)
+    assert limit == pytest.approx((32 << 20) / per, rel=2e-3)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("b,big,d,dtype", [(2000, 65536, 768, "bf16"), (1000, 1100, 512, "f16"),
                                             (3001, 40000, 200, "bf16"), (1500, 33000, 256, "f32"),
