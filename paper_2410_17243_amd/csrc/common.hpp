@@ -131,49 +131,15 @@ __device__ __forceinline__ void mfma_split(const split3& a, const split3& b, f32
   c1 = mfma_bf16(a.p[0], b.p[0], c1);
 }
 
-// Asynchronous 16-byte global -> LDS copy.  Lane L writes LDS bytes
-// [lds_base + 16 L, lds_base + 16 L + 16); lds_base must be wave-uniform.
-__device__ __forceinline__ void dma16(const void* gsrc, INFCL_LDS void* lds_base) {
-  __builtin_amdgcn_global_load_lds((const INFCL_GLOBAL void*)gsrc, lds_base, 16, 0, 0);
-}
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// Wait until at most n (0..63) vector-memory operations of this wave are in
-// flight.  Operations complete in issue order, so this waits for all but the n
-// most recently issued ones.
-__device__ __forceinline__ void wait_dma_allow(int n) {
-  switch (n) {
-#define INFCL_VM_CASE(k) \
-  case k: asm volatile("s_waitcnt vmcnt(" #k ")" ::: "memory"); break;
-    INFCL_VM_CASE(0) INFCL_VM_CASE(1) INFCL_VM_CASE(2) INFCL_VM_CASE(3) INFCL_VM_CASE(4) INFCL_VM_CASE(5)
-    INFCL_VM_CASE(6) INFCL_VM_CASE(7) INFCL_VM_CASE(8) INFCL_VM_CASE(9) INFCL_VM_CASE(10) INFCL_VM_CASE(11)
-    INFCL_VM_CASE(12) INFCL_VM_CASE(13) INFCL_VM_CASE(14) INFCL_VM_CASE(15) INFCL_VM_CASE(16) INFCL_VM_CASE(17)
-    INFCL_VM_CASE(18) INFCL_VM_CASE(19) INFCL_VM_CASE(20) INFCL_VM_CASE(21) INFCL_VM_CASE(22) INFCL_VM_CASE(23)
-    INFCL_VM_CASE(24) INFCL_VM_CASE(25) INFCL_VM_CASE(26) INFCL_VM_CASE(27) INFCL_VM_CASE(28) INFCL_VM_CASE(29)
-    INFCL_VM_CASE(30) INFCL_VM_CASE(31) INFCL_VM_CASE(32) INFCL_VM_CASE(33) INFCL_VM_CASE(34) INFCL_VM_CASE(35)
-    INFCL_VM_CASE(36) INFCL_VM_CASE(37) INFCL_VM_CASE(38) INFCL_VM_CASE(39) INFCL_VM_CASE(40) INFCL_VM_CASE(41)
-    INFCL_VM_CASE(42) INFCL_VM_CASE(43) INFCL_VM_CASE(44) INFCL_VM_CASE(45) INFCL_VM_CASE(46) INFCL_VM_CASE(47)
-#undef INFCL_VM_CASE
-    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-  }
-}
 
-// Raw buffer resource over [base, base + nbytes): loads past the end return 0.
-// Rebased per tile so that 32-bit per-lane offsets address inputs of any size.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t nbytes) {
-  const int64_t n = nbytes < 0 ? 0 : (nbytes > 0xFFFFFFF0ll ? 0xFFFFFFF0ll : nbytes);
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)(uint32_t)n, 0x00020000);
-}
-// 16-byte buffer -> LDS copy; lane L writes LDS bytes [lds_base + 16 L, +16).
-__device__ __forceinline__ void dma16b(__amdgpu_buffer_rsrc_t rs, INFCL_LDS void* lds_base, uint32_t voff,
-                                       uint32_t soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds_base, 16, voff, soff, 0, 0);
-}
-
-// The same copy issued from inline assembly, with a raw descriptor (see
-// rsrc_words).  The compiler does not see this as a write to LDS, so it never
-// stalls later LDS reads on it: the caller waits for completion explicitly
-// (wait_dma / wait_dma_allow) before the written buffer is read.  m0 holds
-// the wave-uniform LDS base.  The compiler's hazard checks do not look inside
+// Asynchronous 16-byte buffer -> LDS copies, issued from inline assembly with a
+// raw descriptor over [base, base + nbytes) (rsrc_words; loads past the end
+// return 0; rebased per tile so that 32-bit per-lane offsets address inputs of
+// any size).  Lane L writes LDS bytes [lds_base + 16 L, +16).  The compiler does
+// not see this as a write to LDS, so it never stalls later LDS reads on it: the
+// caller waits for completion explicitly (wait_dma) before the written buffer is
+// read.  m0 holds the wave-uniform LDS base.  The compiler's hazard checks do not look inside
 // inline assembly, and it may restore an operand right before it (an SGPR of
 // the descriptor with v_readlane, the offset with v_accvgpr_read): the five
 // wait states cover a VALU-written SGPR read by a vector memory instruction,

@@ -81,16 +81,11 @@ struct Fwd2Params {
   int nCT;  // column tiles of 32
 };
 
-// waves per workgroup: 8 (one workgroup per CU, a text tile loaded once per
-// CU) or 4 (two workgroups per CU)
-#ifndef INFCL_FWD2_WAVES
-#define INFCL_FWD2_WAVES 8
-#endif
-constexpr int kF2NW = INFCL_FWD2_WAVES;
-// Waves per workgroup at width d: above 512 the own rows' operand (d/4
-// registers) leaves room for one wave per SIMD only, so 4 waves (128 own
-// rows) and one workgroup per CU.
-__host__ __device__ constexpr int fwd2_waves(int64_t d) { return d > 512 ? 4 : kF2NW; }
+// Waves per workgroup at width d, one workgroup per CU (so that a text tile is
+// loaded once per CU; two workgroups of 4 waves were 3 to 7% slower): 8, two per
+// SIMD; above 512 the own rows' operand (d/4 registers) leaves room for one wave
+// per SIMD only, so 4 (128 own rows).
+__host__ __device__ constexpr int fwd2_waves(int64_t d) { return d > 512 ? 4 : 8; }
 constexpr float kTinyBound = 5.421010862427522e-20f;  // 2^-64
 // mfma16_vgpr with the B operand (the own rows) held in AGPRs, for d > 512;
 // the same wait states around the MFMA.
@@ -215,7 +210,7 @@ __global__ void __launch_bounds__(64 * fwd2_waves(D), D > 512 ? 1 : 2) fwd_sweep
   constexpr int kPreD = D > 512 ? INFCL_F2_PRE_WIDE : INFCL_F2_PRE;
   constexpr int kPre = KS < kPreD ? KS : kPreD;
   static_assert(D % 64 == 0 && D <= 1024 && NIW >= 1 && KS % NIW == 0, "tile DMA layout");
-  static_assert((D > 512 ? 1 : 2) * (2 * TILEB + 4 * 1024 + 5 * 512) <= 160 * 1024, "workgroups per CU");
+  static_assert(2 * TILEB + 2 * 2048 + 2 * 256 * NW + 128 * NW <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(1024))) char tA_[TILEB];
   __shared__ __attribute__((aligned(1024))) char tB_[TILEB];
   // running pairs of the tile's 32 columns: R at [0, 256), l at [256, 512);

@@ -116,7 +116,8 @@ __host__ __device__ __forceinline__ int gp_chunk_off(int row, int c) { return ro
 // PAD = false drops the two leading wait states, for call sites whose source
 // operands are never written by a VALU instruction just before (LDS loads and
 // registers set up before the sweep); the build's wait-state scan checks
-// every site of either form.
+// every site of either form.  The sweeps all do; the padded form serves the
+// ablation's.
 template <bool F16, bool PAD = true>
 __device__ __forceinline__ void mfma16_vgpr(f32x16& acc, const bf16x8& a, const bf16x8& b, bool first, bool last) {
   if constexpr (F16) {
