@@ -31,7 +31,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 BF16_PEAK = 2.5e15      # MI355X dense bf16 MFMA, FLOP/s
-FP32_MFMA_PEAK = 157.3e12
 HBM_PEAK = 8.0e12       # MI355X HBM3E, bytes/s
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "traffic.json")
 PROFILE_MFMA = os.path.join(ROOT, "profiles", "mfma_busy.json")
@@ -299,10 +298,12 @@ def main():
     entries = float(b) * float(b)
     value = entries / (ms_per_step * 1e-3)
     bwd_launch_ms = sum(bwd_ms) / len(bwd_ms) / 2.0   # one side of the two that an infcl_bwd call sweeps
-    # 16-bit inputs with d >= 640 run the wide-row sweeps
-    bwd_kernel = "bwd_f32" if dt_name == "f32" else "bwd_wide" if d >= 640 else "bwd_sweep"
+    # 16-bit inputs with d > 512 run the wide-row sweeps, pipelined up to 768
+    bwd_kernel = ("bwd_f32" if dt_name == "f32" else "bwd_wide" if d > 768 else "bwd_wide3" if d > 512
+                  else "bwd_sweep")
     fwd_launch_ms = sum(fwd_ms) / len(fwd_ms)
-    peak = FP32_MFMA_PEAK if dt_name == "f32" else BF16_PEAK  # fp16 and bf16 dense MFMA peaks are equal
+    # fp16 and bf16 dense MFMA peaks are equal; fp32 products are six bf16 ones each
+    peak = BF16_PEAK / 6.0 if dt_name == "f32" else BF16_PEAK
     alg_bwd_launch = 3.0 * entries * d      # half of the 6 b^2 d algorithmic backward flops
     alg_fwd_launch = 2.0 * entries * d
     achieved = alg_bwd_launch / (bwd_launch_ms * 1e-3)
@@ -310,7 +311,7 @@ def main():
     if a.shards > 1:
         workload += f", as {a.shards} shards"
     fwd_kernel = "fwd_sweep2" if dt_name != "f32" else "fwd_sweep"  # 16-bit widths run padded to a multiple of 128
-    src = source_hash("bwd.hip", "bwd_wide.hip", "bwd.hpp", "sweep.hpp", "common.hpp")
+    src = source_hash("bwd.hip", "bwd_wide.hip", "bwd_f32.hip", "bwd.hpp", "sweep.hpp", "common.hpp")
     traffic = load_traffic(bwd_kernel, workload, src)
     # roofline bound from the arithmetic intensity: flops per HBM byte (the
     # measured bytes when the counters are current, else the compulsory ones:
