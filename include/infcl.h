@@ -122,9 +122,9 @@ infcl_status infcl_fwd(const void* img, const void* txt, int64_t b, int64_t d, i
  * are rounded once, to nearest even, when stored.  Another known type returns
  * INFCL_ERR_UNSUPPORTED, an unknown one INFCL_ERR_INVALID.  dloss is a device
  * pointer to one float (NULL means 1).  lse_r, lse_c and aux must come from
- * infcl_fwd on the same inputs.  Two sweeps run: one owns rows of img and
- * accumulates dimg in registers, the other owns rows of txt; the softmax is
- * never written to memory. */
+ * infcl_fwd on the same inputs.  One launch sweeps both sides: row blocks that
+ * own rows of img and accumulate dimg in registers, and blocks that own rows of
+ * txt; the softmax is never written to memory. */
 infcl_status infcl_bwd(const void* img, const void* txt, int64_t b, int64_t d, int dtype,
                        const float* scale, const float* lse_r, const float* lse_c, const float* aux,
                        const float* dloss, void* dimg, void* dtxt, int grad_dtype, float* dscale,

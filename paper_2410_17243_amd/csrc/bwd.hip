@@ -575,9 +575,20 @@ int launch_bwd_f32(const BwdParams& p, int nwg, hipStream_t stream);
 // that a batch of few blocks, or the remainder of a larger one, still fills
 // the chip (measured, one launch per side before, step with the forward:
 // b = 1024, d = 512 fp32 1834 -> 179 us, b = 4096, d = 768 fp16 456 -> 202 us,
-// b = 8192, d = 256 fp32 4.60 -> 1.44 ms).  ns minimises (rounds of parts) / ns block times plus the cost of
-// a part (prologue, epilogue) and of the reduction, which reads and writes
-// bm x d floats per part; the partial sums take at most cap bytes.
+// b = 8192, d = 256 fp32 4.60 -> 1.44 ms).  ns minimises (rounds of parts) / ns
+// block times plus the cost of a part (prologue, epilogue) and of the reduction,
+// which reads and writes bm x d floats per part; the partial sums take at most
+// cap bytes.
+// The model's constants are rough.  Per tile and feature 3.7e-3 us is the
+// 128-row sweep's (3.6e-3 at b = 32768, d = 512, 4.1e-3 at 256, 4.9e-3 at 128, of
+// two workgroups per CU there) and 0.011 the fp32 sweep's (0.0106 at b = 8192,
+// d = 512, 0.0119 at 256); the wide sweeps' blocks of half the rows take
+// 1.9e-3 (b = 131072, d = 768), so that they split a little further.  A part's
+// fixed 8 us is about half of what kernel traces show at small batches (15 us at
+// b = 256 and 18 at 1000, d = 512), and 2e6 bytes per us about half the rate of
+// the writes and the reduction's reads together (4 to 14 us for 3 to 50 MB).  One
+// workgroup per compute unit is counted at every width, although at 16-bit
+// d = 128 and fp32 d up to 192 two or three are resident.
 constexpr int kCUs = 256;
 BwdPlan plan_bwd(int64_t b, int64_t nrows, int64_t d, int dtype, size_t cap) {
   BwdPlan pl;

@@ -10,9 +10,10 @@
 // register file, so a workgroup owns 64 rows instead: 64 x d fp32 is d/4
 // AGPRs per wave.  (The 128-row sweep in passes of 128 features, each
 // recomputing GEMM1, took 5.8 ms per side at b = 10007, d = 640, before both
-// this form and the split of row blocks; this form 0.44 ms for both sides.)  GEMM1's own operand is then split by contraction: the
-// wave pair (2 ob, 2 ob + 1) holds own block ob (32 rows), each wave every
-// other 16-feature step (d/8 VGPRs), and computes a partial S^T block over its half.
+// bwd_wide3 and the split of row blocks; with them 0.55 ms for both sides.)
+// GEMM1's own operand is then split by contraction: the wave pair (2 ob,
+// 2 ob + 1) holds own block ob (32 rows), each wave every other 16-feature step
+// (d/8 VGPRs), and computes a partial S^T block over its half.
 // Per tile:
 //   GEMM1   partial S^T (32 swept x 32 own) over the wave's feature half
 //           (and the DMA of the next tile's log-sum-exp slot);
@@ -345,7 +346,8 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Pipelined form for d = 768, where three swept tiles fit in LDS (3 x 48 KiB).
+// Pipelined form for d = 640 and 768, where three swept tiles fit in LDS (3 x 40
+// or 48 KiB).
 // Same quantities and the same per-entry arithmetic as bwd_wide; the work of
 // three tiles overlaps in each iteration t, with two barriers per tile:
 //   stage 1  GEMM1 of tile t+1 (partial S^T over the wave's feature half),
@@ -370,8 +372,8 @@ __global__ void __launch_bounds__(256, 1) bwd_wide(BwdParams p) {
 // earlier), read by GEMM1 in iteration t-1 and by GEMM2 in iteration t.  The
 // swept log-sum-exp values a lane needs for tile t are loaded into registers
 // in iteration t-1.
-// At d = 1024 three tiles (3 x 64 KiB) do not fit in LDS: bwd_wide serves it.
-// It serves d = 768 at every batch size: measured against bwd_wide, 4% faster
+// At d = 896 and 1024 three tiles (3 x 56 or 64 KiB) do not fit in LDS: bwd_wide
+// serves those.  This form serves d = 768 at every batch size: measured against bwd_wide, 4% faster
 // at b = 131072 (192 MiB of swept rows, inside the 256 MiB last-level
 // cache) and 1.5-1.6% faster at b = 163840, 262144 and 1048576, where the
 // tiles come from HBM.
